@@ -352,10 +352,10 @@ def run_batch_bench(args, w):
                                      f"instances 0, {stride + 1}, {2 * (stride + 1)}, ... of the batch")
     out = {"metric": "spin-updates/s", "value": value, "unit": "spin-updates/s", "n_gpus": 1, "steps": args.steps,
            "warmup": args.warmup, "ms_per_step": 1000 * wall / args.steps, "higher_is_better": True,
-           "scaling": "weak", "vs_baseline": None, "dtype": "fp8xfp4" if kernel == "k_batch_fp4" else "i8",
+           "scaling": "weak", "vs_baseline": None, "dtype": "fp4xfp4" if kernel == "k_batch_fp4" else "i8",
            "data": "synthetic",
            "config": {"workload": w["desc"], "instances": n, "replicas": R, "hmc_steps": T, "path": "i8",
-                      "operands": "FP8 spins x FP4 couplings (exact for integer couplings in the FP4 set)",
+                      "operands": "FP4 spins x FP4 couplings (exact for integer couplings in the FP4 set)",
                       "schedule": s, "spin_updates_per_step": su, "sweep_kernel": kernel},
            "roofline": {"bound": "alu", "achieved": achieved, "peak": VALU_OPS_PEAK, "unit": "ops/s",
                         "frac": achieved / VALU_OPS_PEAK,

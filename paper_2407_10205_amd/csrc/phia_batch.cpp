@@ -275,9 +275,9 @@ struct phia_batch {
     // persistent sweep
     BatchInst* dinst = nullptr;
     BatchItem* ditems = nullptr;
-    int nitems = 0;
+    int nteam = 0, nsquad = 0;  // items run by whole workgroups and by squads
     int* dqueue = nullptr;
-    size_t fp4_lds = 0;
+    size_t team_lds = 0, squad_lds = 0;
     int n_fp4 = 0;
     // one-item-per-workgroup sweep of the remaining instances
     SweepArgs* dtab = nullptr;
@@ -444,7 +444,6 @@ phia_status phia_batch_create(phia_problem* const* probs, int32_t count, const i
             a.bestE = p->dbestE;
             a.bestS = p->dbestS;
             a.bestStep = p->dbestStep;
-            a.k0 = 0;
             a.k1 = steps[i];
             a.L = p->L;
             a.eps = p->eps;
@@ -453,9 +452,6 @@ phia_status phia_batch_create(phia_problem* const* probs, int32_t count, const i
             a.Np = p->Np;
             a.R = replicas[i];
             a.deriv = p->deriv;
-            a.init = 1;
-            const bool dbl = batch_fp4_lds_bytes(p->Np, true) <= static_cast<size_t>(kLdsMax);
-            b->fp4_lds = std::max(b->fp4_lds, batch_fp4_lds_bytes(p->Np, dbl));
             for (int blk = 0; blk < p->geo.nblocks; ++blk) {
                 items.push_back(BatchItem{static_cast<int32_t>(insts.size()), blk});
                 const int rows = std::min(kBatchRows, replicas[i] - blk * kBatchRows);
@@ -501,18 +497,37 @@ phia_status phia_batch_create(phia_problem* const* probs, int32_t count, const i
         }
     }
     b->n_fp4 = static_cast<int>(insts.size());
-    // Persistent sweep items: costliest first, so that the queue's tail holds
-    // the shortest items.
+    // Persistent sweep items, costliest first so that the queues' tails hold
+    // the shortest items.  Two small items at a time on a CU finish more per
+    // second (256 columns: 1.88 us per item and step against 1.97 for one item
+    // by the whole workgroup, 64 columns: 0.65 against 1.04), one at a time
+    // each of them sooner, so squads run them only where the CUs get more than
+    // a round of pairs; with fewer the longest CU decides (instances of 32 to
+    // 512 columns, 5000 steps: 512 of them 29.0 against 33.6 ms with squads,
+    // 2048 of them 102 against 94 ms).
     {
+        auto small = [&](size_t t) { return batch_fp4_squad(insts[static_cast<size_t>(items[t].inst)].Np); };
+        size_t nsmall = 0;
+        for (size_t t = 0; t < items.size(); ++t) nsmall += small(t) ? 1 : 0;
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
+        const bool squads = nsmall >= 3 * static_cast<size_t>(cus);
         std::vector<size_t> ord(items.size());
         for (size_t t = 0; t < ord.size(); ++t) ord[t] = t;
-        std::stable_sort(ord.begin(), ord.end(), [&](size_t u, size_t w) { return item_cost[u] > item_cost[w]; });
+        auto team = [&](size_t t) { return !squads || !small(t); };
+        std::stable_sort(ord.begin(), ord.end(), [&](size_t u, size_t w) {
+            return team(u) != team(w) ? team(u) : item_cost[u] > item_cost[w];
+        });
         std::vector<BatchItem> sorted;
         sorted.reserve(items.size());
-        for (size_t t : ord) sorted.push_back(items[t]);
+        for (size_t t : ord) {
+            ++(team(t) ? b->nteam : b->nsquad);
+            size_t& lds = team(t) ? b->team_lds : b->squad_lds;
+            lds = std::max(lds, batch_fp4_lds_bytes(insts[static_cast<size_t>(items[t].inst)].Np, !team(t)));
+            sorted.push_back(items[t]);
+        }
         items.swap(sorted);
     }
-    b->nitems = static_cast<int>(items.size());
     if (!items.empty()) {
         if ((e = hipMalloc(&b->dinst, sizeof(BatchInst) * insts.size())) != hipSuccess ||
             (e = hipMalloc(&b->ditems, sizeof(BatchItem) * items.size())) != hipSuccess ||
@@ -543,7 +558,7 @@ phia_status phia_batch_create(phia_problem* const* probs, int32_t count, const i
             if ((e = prepare_sweep_batch(kv.second.path, kv.second.cbw, kv.second.mh, kv.second.lds)) != hipSuccess)
                 return bail(hip_fail(nullptr, e, "kernel attributes"));
     }
-    if (b->nitems > 0 && batch_fp4_grid(b->fp4_lds) < 1)
+    if (!items.empty() && batch_fp4_grid(b->team_lds, b->squad_lds) < 1)
         return bail(fail(PHIA_EDEVICE, "the persistent batch sweep does not fit the device"));
     // schedules and state set-up above ran on the problems' streams
     if ((e = hipDeviceSynchronize()) != hipSuccess) return bail(hip_fail(nullptr, e, "state set-up"));
@@ -551,10 +566,8 @@ phia_status phia_batch_create(phia_problem* const* probs, int32_t count, const i
     if ((e = hipStreamBeginCapture(b->st, hipStreamCaptureModeThreadLocal)) != hipSuccess)
         return bail(hip_fail(nullptr, e, "graph capture"));
     hipError_t le = hipSuccess;
-    if (b->nitems > 0) {
-        le = launch_batch_queue_reset(b->dqueue, b->st);
-        if (le == hipSuccess) le = launch_batch_fp4(b->dinst, b->ditems, b->nitems, b->dqueue, b->fp4_lds, b->st);
-    }
+    if (!items.empty())
+        le = launch_batch_fp4(b->dinst, b->ditems, b->nteam, b->nsquad, b->dqueue, b->team_lds, b->squad_lds, b->st);
     if (le == hipSuccess && !init_tab.empty()) le = launch_init_batch(b->dtab, static_cast<int>(init_tab.size()), b->st);
     size_t bi = 0;
     for (auto& kv : buckets) {

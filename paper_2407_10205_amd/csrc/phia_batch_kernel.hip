@@ -9,22 +9,33 @@
 // cores, exact energy, records, kick), exactly as the other sweep kernels
 // compute it.
 //
-// Layout.  Eight waves; wave w owns column blocks c = w + 8 cw (16 columns
-// each) of both 16-replica row tiles, with x, v and the MFMA accumulators of
-// its elements in VGPRs in the 16x16 MFMA output layout (lane l: column l %
-// 16, rows 4 (l / 16) + j).  The coupling slice of the instance sits in LDS
-// as FP4 fragments for the whole item; the spins go to LDS as FP8 bytes
-// (+1 = 0x38, -1 = 0xB8) in the k order of the FP4 fragments, and J.s runs
-// on v_mfma_scale_f32_16x16x128_f8f6f4 (FP8 spins x FP4 couplings, FP32
-// accumulation, scales 1): every product and partial sum is an integer
-// below 2^24, so the field is exact, and it stays in FP32 for the kick and
-// the energy terms (their sums are integers below 2^24 too: host-checked).
-// Row energies are summed by DPP within a wave and by LDS atomics over the
-// waves; the records of step k are taken
-// in step k + 1 after the step's only barrier.  x is drawn here when an item
-// starts a fresh anneal (no separate init kernel).
+// Layout.  Eight waves; the products run transposed, D = J . S^T, with the
+// couplings as the A operand and the spins as the B operand of
+// v_mfma_scale_f32_16x16x128_f8f6f4 (FP4 x FP4, scales 1, FP32 accumulation
+// starting from the fields h): every product and partial sum is an integer
+// below 2^24 (host-checked), so the field is exact and stays in FP32 for the
+// kick and the energy terms.  A tile is one 16-column block of one of the two
+// 16-replica halves; lane (lr, lg) = (lane % 16, lane / 16) of its wave holds
+// replica lr and four of the block's columns, x, v and the field in VGPRs.  A
+// replica's record, its energy partial (a sum over four lanes) and its spins
+// (four FP4 codes, one 16-bit LDS store) are then per-lane work; with a
+// column per lane and four replicas per lane they took 27 of the 55 VALU
+// instructions per spin-update.  Of ncb column blocks every wave owns ncb / 8
+// for both halves, and when four are left over wave w owns block w % 4 of
+// them for half w / 4, so that all waves carry the same number of tiles.
+//
+// The couplings of the instance sit in LDS as FP4 fragments for the whole
+// item (128 KiB at Np = 512), the spins of the step in two LDS buffers by
+// step parity, so a step has one barrier; the records of step k are taken in
+// step k + 1.  x is drawn here when an item starts a fresh anneal (no
+// separate init kernel).
+//
+// The step is bound by VALU issue.  Its FP32 operations read VGPRs and inline
+// constants only (2 cycles per wave; 4 with an SGPR operand, see in_vgpr).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include <type_traits>
 
@@ -36,407 +47,700 @@ namespace phia {
 
 namespace {
 
-constexpr int kBW = 8;                 // waves per workgroup
+constexpr int kBW = 16;                // waves per workgroup
 constexpr int kBT = 64 * kBW;          // threads per workgroup
-constexpr uint32_t kFixedLds = 512;    // energy sums [3][32] int32, the item slot
-constexpr uint32_t kSpinPlus = 0x38u;  // FP8 E4M3 +1.0
-constexpr uint32_t kSpinMinus = 0xB8u; // FP8 E4M3 -1.0
+constexpr int kSquad = 8;              // waves per squad
+constexpr int kSquadMaxNp = 256;       // largest instance of a squad
+// Energy sums [3][32] float, the item slot (byte 384), a squad's barrier
+// counter (byte 400).
+constexpr uint32_t kFixedLds = 512;
 
 __host__ __device__ inline int nkb4_of(int Np) { return (Np + 127) / 128; }
-__host__ __device__ inline uint32_t srow_of(int Np) { return static_cast<uint32_t>(nkb4_of(Np)) * 128u + 16u; }
-__host__ __device__ inline uint32_t jbytes_of(int Np)
+// A pointer that every lane of the wave holds alike, as a scalar (the
+// arguments of a function that is not inlined arrive in VGPRs).
+template <class T>
+__device__ __forceinline__ T* uniform_ptr(T* p)
 {
-    return static_cast<uint32_t>(Np / 16) * static_cast<uint32_t>(nkb4_of(Np)) * 1024u;
-}
-__host__ __device__ inline uint32_t sbytes_of(int Np) { return static_cast<uint32_t>(kBatchRows) * srow_of(Np); }
-
-// Initial position draw (a call, so that the element loops do not hold many
-// generator states at once).
-__device__ __attribute__((noinline)) float gauss_x(uint64_t seed, uint64_t replica, int i)
-{
-    return dev_gauss(seed, kTagX, replica, 0, static_cast<uint64_t>(i));
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32));
+    return reinterpret_cast<T*>(static_cast<uint64_t>(hi) << 32 | lo);
 }
 
-// All 8 draws of one momentum block (a call for the same reason).
-struct Draws8 {
-    float g[8];
+// LDS passed to a function that is not inlined keeps its address space (a
+// generic pointer would turn every access into a flat one).
+typedef __attribute__((address_space(3))) unsigned char LdsByte;
+
+// The kick factors as scalar loads (a flat load would count as an LDS access
+// too, and the step's first LDS wait would wait for it).
+typedef const __attribute__((address_space(4))) float* ConstF;
+__device__ __forceinline__ ConstF scalar_table(const float* p)
+{
+    return (ConstF)(uint64_t)uniform_ptr(p);
+}
+
+// Column of element j (0 .. 3) of lane group lg within its 16-column block.
+// The FP4 codes of 8 columns are ordered 0 4 1 5 2 6 3 7 in LDS (the packed
+// couplings' k order), so the columns whose codes a lane stores as one
+// 16-bit word are 8 (lg / 2) + 2 (lg % 2) + {0, 4, 1, 5}.
+__device__ __forceinline__ int col_of(int lg, int j)
+{
+    return 8 * (lg >> 1) + 2 * (lg & 1) + (j >> 1) + 4 * (j & 1);
+}
+
+// vdst's odd rows of 16 lanes exchanged with vsrc's even rows (permlane16),
+// or its upper 32 lanes with vsrc's lower 32 (permlane32).  The nop covers
+// the VALU-write-to-permlane-read hazard; the whole wave must be active.
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b)
+{
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b)
+{
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+
+// Gaussian draws of this lane's four columns of one column block for one
+// replica (a call, so that the step does not hold generator states).  The
+// block of 8 columns c8 belongs to the lane pair lg, lg ^ 1; the lane's
+// columns take the even-numbered (lg even) or odd-numbered words' pairs.
+struct Draws4 {
+    float g[4];
 };
-__device__ __attribute__((noinline)) Draws8 gauss_block8(uint64_t seed, uint64_t replica, uint64_t round, uint64_t c8)
+struct Draws8 {
+    float a[4], b[4];
+};
+__device__ __forceinline__ Draws4 draws_of(uint32_t lo0, uint32_t hi0, uint32_t lo1, uint32_t hi1)
 {
+    Draws4 d;
+    gauss_pair(static_cast<uint64_t>(hi0) << 32 | lo0, d.g[0], d.g[2]);
+    gauss_pair(static_cast<uint64_t>(hi1) << 32 | lo1, d.g[1], d.g[3]);
+    return d;
+}
+__device__ __attribute__((noinline)) Draws4 draws_one(uint64_t seed, uint32_t tag, uint64_t replica, uint64_t round,
+                                                       uint64_t c8, int odd)
+{
+    const u64x4 o = dev_philox(c8, round, replica, tag, seed, 0);
+    const uint64_t w0 = odd ? o.w[1] : o.w[0], w1 = odd ? o.w[3] : o.w[2];
+    return draws_of(static_cast<uint32_t>(w0), static_cast<uint32_t>(w0 >> 32), static_cast<uint32_t>(w1),
+                    static_cast<uint32_t>(w1 >> 32));
+}
+// The same for two generator blocks (replica ra or rb, column block c8a or
+// c8b): the even lane of a pair runs the generator for the first, the odd lane
+// for the second, and a lane swap hands each the words it transforms.
+__device__ __forceinline__ Draws8 draws_pair(uint64_t seed, uint32_t tag, uint64_t r, uint64_t round, uint64_t c8)
+{
+    const u64x4 o = dev_philox(c8, round, r, tag, seed, 0);
+    uint32_t l[4], h[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        l[q] = static_cast<uint32_t>(o.w[q]);
+        h[q] = static_cast<uint32_t>(o.w[q] >> 32);
+    }
+    swap16(l[0], l[1]);
+    swap16(h[0], h[1]);
+    swap16(l[2], l[3]);
+    swap16(h[2], h[3]);
+    const Draws4 p = draws_of(l[0], h[0], l[2], h[2]), q = draws_of(l[1], h[1], l[3], h[3]);
     Draws8 d;
-    gauss_block(seed, replica, round, c8, d.g);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        d.a[j] = p.g[j];
+        d.b[j] = q.g[j];
+    }
     return d;
 }
 
-// The steps of one work item for a wave that owns NCW column blocks of an
-// instance with NKB k blocks of 128 (NCW = 0: a wave without columns, which
-// only keeps the workgroup's barriers).
-template <int NKB, int NCW>
-__device__ __attribute__((noinline)) void batch_item(const BatchInst& a, int blk, unsigned char* lds, bool dbuf, int wave,
-                                           int lane)
+// two replicas (r0 and r0 + 16) of one column block
+__device__ __attribute__((noinline)) Draws8 draws_both(uint64_t seed, uint32_t tag, uint64_t r0, uint64_t round,
+                                                       uint64_t c8, int odd)
 {
-    constexpr int MT = 2;
-    constexpr uint32_t srow = NKB * 128u + 16u;
-    constexpr uint32_t sb = kBatchRows * srow;
-    const uint32_t jb = static_cast<uint32_t>(a.Np / 16) * NKB * 1024u;
-    float* sE = reinterpret_cast<float*>(lds);  // [3][32] row energy sums of steps k mod 3 (exact integers)
+    return draws_pair(seed, tag, r0 + (odd ? 16 : 0), round, c8);
+}
+// two column blocks of one replica
+__device__ __attribute__((noinline)) Draws8 draws_two(uint64_t seed, uint32_t tag, uint64_t r, uint64_t round,
+                                                      uint64_t c8a, uint64_t c8b, int odd)
+{
+    return draws_pair(seed, tag, r, round, odd ? c8b : c8a);
+}
+
+// The steps of one work item.  Two teams of eight waves, one per replica half,
+// run one phase apart: while one team's waves take the field of their half on
+// the matrix cores and its energy sums (P), the other team's take the records,
+// the kick and the next drift (V), and a workgroup barrier closes each phase.
+// A wave issues at most one instruction per 4 cycles, so the two waves per
+// SIMD of the V team reach the VALUs' rate only while nothing else holds them
+// up: the operand reads, the products and the waits for them are the other
+// team's.  Eight waves that did both in one phase per step took 4.64 us per
+// step at N = 512, with the halves' products and kicks interleaved in each
+// wave 3.97 us, in this form 3.66 us (a column per lane and FP8 spins, before
+// that: 5.8 us).  Without the kick a step takes 1.85 us, without the products
+// 3.1 us: the kick runs at 2.1 cycles per instruction and SIMD, and an MFMA
+// (16 cycles here) leaves the SIMD's VALU idle while it issues.
+//
+// The wave owns the column blocks tw + 8 c, c < NC, and the k range is NC
+// blocks of 128: the caller pads the couplings in LDS to 8 NC column blocks.
+template <int NC, int DERIV>
+__device__ __attribute__((noinline)) void team_item(const BatchInst* ap, int blk, LdsByte* lds3, int wave, int lane)
+{
+    unsigned char* const lds = (unsigned char*)lds3;
+    constexpr int NF = NC, NKB = NC;
+    constexpr uint32_t srow = NKB * 64u + 16u;
+    wave = __builtin_amdgcn_readfirstlane(wave);
+    blk = __builtin_amdgcn_readfirstlane(blk);
+    const int team = wave >> 3, tw = wave & 7;
+    const BatchInst& a = *uniform_ptr(ap);
+    const int Np = __builtin_amdgcn_readfirstlane(a.Np), N = __builtin_amdgcn_readfirstlane(a.N);
+    constexpr uint32_t jb = 8u * NC * NKB * 1024u;
+    float* sE = reinterpret_cast<float*>(lds) + team * 32;  // [2 parities][16] row energy sums (exact integers)
     unsigned char* sJ = lds + kFixedLds;
-    unsigned char* sS = lds + kFixedLds + jb;       // [dbuf ? 2 : 1][32][srow] FP8 spins
-    const int nsteps = static_cast<int>(a.k1 - a.k0);
+    unsigned char* S = sJ + jb + team * 16u * srow;  // [16][srow] FP4 spins of the team's half
+    const int lr = lane & 15, lg = lane >> 4;
+    // fields of the lane's columns of column block 0, in lane order
+    const v4f* sH = reinterpret_cast<const v4f*>(sJ + jb + 32u * srow) + lg;
+    const int nsteps = __builtin_amdgcn_readfirstlane(static_cast<int>(a.k1));
+    const uint64_t seed = *a.seed;
+    auto cbt = [&](int c) { return tw + 8 * c; };  // column block of tile c
+    const int64_t gr = static_cast<int64_t>(blk) * kBatchRows + 16 * team + lr;  // the lane's replica
+    const bool rok = gr < a.R;
+    float x[NC][4], v[NC][4], sg[NC][4];
+    v4f I[NC];
+    uint32_t bp[NC];            // record spins: the four FP4 codes of each tile
+    float bE = __builtin_inff();  // record energy (+inf: none yet)
+    int32_t bK = -1;
+    // draws of a generator round (0 in padding); two column blocks share
+    // their generator blocks between the lane pairs
+    auto draw = [&](uint32_t tag, uint64_t round, float (&y)[NC][4]) {
+        const auto c8 = [&](int c) { return static_cast<uint64_t>(cbt(c)) * 2 + (lg >> 1); };
+        const auto put = [&](float (&d)[4], int c, const float (&g)[4]) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[j] = (cbt(c) * 16 + col_of(lg, j) < N && rok) ? g[j] : 0.0f;
+        };
+#pragma unroll
+        for (int c = 0; c + 1 < NF; c += 2) {
+            const Draws8 d = draws_two(seed, tag, static_cast<uint64_t>(gr), round, c8(c), c8(c + 1), lg & 1);
+            put(y[c], c, d.a);
+            put(y[c + 1], c + 1, d.b);
+        }
+        if constexpr (NF % 2 == 1) {
+            const Draws4 d = draws_one(seed, tag, static_cast<uint64_t>(gr), round, c8(NF - 1), lg & 1);
+            put(y[NF - 1], NF - 1, d.g);
+        }
+    };
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        bp[c] = 0x2222u;
+        I[c] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            x[c][j] = v[c][j] = 0.0f;
+            sg[c][j] = 1.0f;
+        }
+    }
+    draw(kTagX, 0, x);
 
-    if constexpr (NCW == 0) {
-        for (int s = 0; s <= nsteps; ++s) {
-            if (!dbuf && s > 0) __syncthreads();
-            __syncthreads();
+    const float eps = in_vgpr(a.eps), gamma = in_vgpr(a.gamma);
+    Sech2K sk{};
+    if constexpr (DERIV == 0) sk = sech2_in_vgprs();
+    const int L = static_cast<int>(a.L < INT32_MAX ? a.L : INT32_MAX);
+    const ConstF ctab = scalar_table(a.ctab);
+    // the lane's codes of column block 0
+    unsigned char* const srow0 = S + static_cast<uint32_t>(lr) * srow + 2u * lg;
+    const unsigned char* const brow = S + lr * srow + 16 * lg;
+    const unsigned char* const jl =
+        sJ + ((lane & 48) + 8 * (lr >> 3) + 2 * ((lr >> 2) & 1) + ((lr >> 1) & 1) + 4 * (lr & 1)) * 16;
+
+    // Drift and readout for step q: momentum refresh, x, spins (FP4 codes).
+    int next_ref = 0, round = 0;
+    auto drift = [&](int q) {
+        if (q == next_ref) {
+            draw(kTagV, static_cast<uint64_t>(round), v);
+            ++round;
+            next_ref = L > INT32_MAX - q ? INT32_MAX : q + L;
         }
-        return;
-    } else {
-        const int lr = lane & 15, lg = lane >> 4;
-        const int Np = a.Np, N = a.N;
-        const int64_t rb0 = static_cast<int64_t>(blk) * kBatchRows;
-        const uint64_t seed = *a.seed;
-        int col[NCW];
-        float hf[NCW], h2f[NCW];
-        bool creal[NCW];
 #pragma unroll
-        for (int cw = 0; cw < NCW; ++cw) {
-            col[cw] = (wave + kBW * cw) * 16 + lr;
-            creal[cw] = col[cw] < N;
-            const int hv = a.h[col[cw]];
-            hf[cw] = static_cast<float>(hv);
-            h2f[cw] = static_cast<float>(2 * hv);
-        }
-        // rows of this lane: rb0 + mt 16 + 4 lg + j; bit mt 4 + j set when < R
-        uint32_t rmask = 0;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                rmask |= (rb0 + mt * 16 + 4 * lg + j < a.R ? 1u : 0u) << (mt * 4 + j);
-        float x[MT][NCW][4], v[MT][NCW][4];
-        float bE[MT][4];    // record energy (+inf: none yet)
-        int32_t bK[MT][4];
-        uint32_t bestbits = 0;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int c = 0; c < NC; ++c) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const bool ok = (rmask >> (mt * 4 + j)) & 1u;
-                const int64_t gr = rb0 + mt * 16 + 4 * lg + j;
-                if (a.init) {
-                    bE[mt][j] = __builtin_inff();
-                    bK[mt][j] = -1;
-                } else {
-                    const int64_t b = ok ? a.bestE[gr] : INT64_MAX;
-                    bE[mt][j] = b == INT64_MAX ? __builtin_inff() : static_cast<float>(b);
-                    bK[mt][j] = ok ? static_cast<int32_t>(a.bestStep[gr]) : -1;
-                }
-#pragma unroll
-                for (int cw = 0; cw < NCW; ++cw) {
-                    const int64_t idx = gr * Np + col[cw];
-                    if (a.init) {
-                        x[mt][cw][j] = (ok && creal[cw]) ? gauss_x(seed, static_cast<uint64_t>(gr), col[cw]) : 0.0f;
-                        v[mt][cw][j] = 0.0f;
-                    } else {
-                        x[mt][cw][j] = ok ? a.x[idx] : 0.0f;
-                        v[mt][cw][j] = ok ? a.v[idx] : 0.0f;
-                        if (ok && creal[cw] && a.bestS[idx] > 0) bestbits |= 1u << ((mt * NCW + cw) * 4 + j);
-                    }
-                }
+                x[c][j] = __builtin_fmaf(eps, v[c][j], x[c][j]);
+                sg[c][j] = x[c][j] >= 0.0f ? 1.0f : -1.0f;
             }
-        const float eps = a.eps, gamma = a.gamma;
-        const int64_t ref0 = a.k0 + (a.L - a.k0 % a.L) % a.L;
-        int64_t next_ref = ref0;
-        uint64_t round = static_cast<uint64_t>(ref0 / a.L);
-        // byte offset of this lane's spin of row 4 lg, column block 0, in the
-        // FP4 k order (columns 0 4 1 5 2 6 3 7 in each group of 8)
-        const int q7 = lr & 7;
-        const uint32_t sbase = 4u * lg * srow + 8u * (lr >> 3) + static_cast<uint32_t>(q7 < 4 ? 2 * q7 : 2 * q7 - 7) +
-                               16u * wave;
-        // signs of the step before the current one, bit (mt NCW + cw) 4 + j
-        uint32_t pm = 0;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int cw = 0; cw < NCW; ++cw)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (x[mt][cw][j] >= 0.0f) pm |= 1u << ((mt * NCW + cw) * 4 + j);
-
-        int r3 = static_cast<int>(a.k0 % 3);
-        for (int s = 0; s <= nsteps; ++s) {
-            const int64_t k = a.k0 + s;
-            const bool last = (s == nsteps);
-            const int r3p = (r3 == 0) ? 2 : r3 - 1, r3n = (r3 == 2) ? 0 : r3 + 1;
-            unsigned char* S = sS + (dbuf ? static_cast<uint32_t>(k & 1) * sb : 0u);
-            const uint32_t pprev = pm;  // signs of step k - 1
-            if (!dbuf && s > 0) __syncthreads();  // every wave has read the spins of step k - 1
-            if (!last) {
-                if (k == next_ref) {
-                    // Momentum refresh (the draws of `round`): the wave's 2 NCW
-                    // tiles fill 32 Philox blocks each; pass hp covers tiles
-                    // 2 hp and 2 hp + 1, lane L generating the block of replica
-                    // row (L >> 1) & 15, 8-column half L & 1 of tile
-                    // 2 hp + (L >> 5), and every element reads its draw from
-                    // that lane.
-#pragma unroll
-                    for (int hp = 0; hp < NCW; ++hp) {
-                        const int u = 2 * hp + (lane >> 5), mtl = u / NCW, cwl = u % NCW;
-                        const Draws8 d = gauss_block8(seed, static_cast<uint64_t>(rb0 + mtl * 16 + ((lane >> 1) & 15)),
-                                                      round, static_cast<uint64_t>(wave + kBW * cwl) * 2 + (lane & 1));
-                        const float* g = d.g;
-#pragma unroll
-                        for (int e = 8 * hp; e < 8 * hp + 8; ++e) {
-                            const int mt = e / (NCW * 4), cw = (e >> 2) % NCW, j = e & 3;
-                            const int src = ((mt * NCW + cw) & 1) * 32 + 2 * (4 * lg + j) + (lr >> 3);
-                            float t = 0.0f;
-#pragma unroll
-                            for (int r = 0; r < 8; ++r) {
-                                const float tr = lane_read(src, g[r]);
-                                t = q7 == r ? tr : t;
-                            }
-                            v[mt][cw][j] = (creal[cw] && ((rmask >> (mt * 4 + j)) & 1u)) ? t : 0.0f;
-                        }
-                    }
-                    next_ref += a.L;
-                    ++round;
-                }
-                // Drift and readout; the spins go to LDS for the product.
-                pm = 0;
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int cw = 0; cw < NCW; ++cw)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            x[mt][cw][j] = __builtin_fmaf(eps, v[mt][cw][j], x[mt][cw][j]);
-                            const bool pos = x[mt][cw][j] >= 0.0f;
-                            pm |= (pos ? 1u : 0u) << ((mt * NCW + cw) * 4 + j);
-                            S[sbase + (mt * 16 + j) * srow + 128u * cw] =
-                                static_cast<unsigned char>(pos ? kSpinPlus : kSpinMinus);
-                        }
-            }
-            __syncthreads();  // spins of step k and energy sums of step k - 1 complete
-
-            // Records of step k - 1 (App. B, Table 3, state 5): every lane that
-            // holds a row takes the same decision.
-            if (s > 0) {
-                float E[MT][4];
-                uint32_t impm = 0;
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const float4 t4 = *reinterpret_cast<const float4*>(sE + r3p * 32 + mt * 16 + 4 * lg);
-                    const float tot[4] = {t4.x, t4.y, t4.z, t4.w};
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        E[mt][j] = -0.5f * tot[j];  // the sum is even: exact
-                        if (E[mt][j] < bE[mt][j]) impm |= 1u << (mt * 4 + j);
-                    }
-                }
-                // Late in an anneal few steps improve a record: the updates
-                // run only when some row of the wave improved (uniform branch).
-                if (__any(impm != 0)) {
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const bool imp = (impm >> (mt * 4 + j)) & 1u;
-                            bE[mt][j] = imp ? E[mt][j] : bE[mt][j];
-                            bK[mt][j] = imp ? static_cast<int32_t>(k - 1) : bK[mt][j];
-                            uint32_t rowmask = 0;
-#pragma unroll
-                            for (int cw = 0; cw < NCW; ++cw) rowmask |= 1u << ((mt * NCW + cw) * 4 + j);
-                            bestbits = imp ? ((bestbits & ~rowmask) | (pprev & rowmask)) : bestbits;
-                        }
-                }
-            }
-            if (last) break;
-            if (wave == 0 && lane < 32) sE[r3n * 32 + lane] = 0.0f;  // read two steps ago
-            const float ck = a.ctab[k];
-
-            // J.s on matrix cores: FP8 spins x FP4 couplings over the k blocks.
-            v4f acc[MT][NCW];
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int cw = 0; cw < NCW; ++cw) acc[mt][cw] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-            {
-                // Operand k order of v_mfma_scale_f32_16x16x128_f8f6f4: FP4 nibble
-                // t of lane group g (the couplings) is k = 32 g + t; FP8 byte t
-                // (the spins) is k = 16 g + t for t < 16 and 64 + 16 g + t - 16
-                // above.  So a lane's spin operand is the 16 bytes at 16 g and
-                // the 16 bytes at 64 + 16 g of the row's 128-wide k block.
-                const unsigned char* arow = S + lr * srow + 16 * lg;
-                const unsigned char* jl = sJ + lane * 16 + static_cast<uint32_t>(wave * NKB) * 1024u;
-#pragma unroll
-                for (int kb = 0; kb < NKB; ++kb) {
-                    v8i A[MT];
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        const v4i lo = *reinterpret_cast<const v4i*>(arow + mt * 16 * srow + kb * 128);
-                        const v4i hi = *reinterpret_cast<const v4i*>(arow + mt * 16 * srow + kb * 128 + 64);
-                        A[mt] = v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                    }
-#pragma unroll
-                    for (int cw = 0; cw < NCW; ++cw) {
-                        const v4i b = *reinterpret_cast<const v4i*>(jl + (kBW * cw * NKB + kb) * 1024u);
-                        const v8i b8 = v8i{b[0], b[1], b[2], b[3], 0, 0, 0, 0};
-#pragma unroll
-                        for (int mt = 0; mt < MT; ++mt)
-                            acc[mt][cw] =
-                                __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[mt], b8, acc[mt][cw], 0, 4, 0, 127,
-                                                                                 0, 127);
-                    }
-                    // keep the operand loads of later k blocks from piling up in registers
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            float I[MT][NCW][4];  // field J s + h, an exact integer in FP32
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int cw = 0; cw < NCW; ++cw)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) I[mt][cw][j] = acc[mt][cw][j] + hf[cw];
-
-            // Kick (mode branch outside the element loops).
-            auto kick_all = [&](auto mode) {
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int cw = 0; cw < NCW; ++cw)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            v[mt][cw][j] = kick_tf<decltype(mode)::value>(x[mt][cw][j], v[mt][cw][j], I[mt][cw][j],
-                                                                         ck, eps, gamma);
-            };
-            if (a.deriv)
-                kick_all(std::integral_constant<int, 1>{});
-            else
-                kick_all(std::integral_constant<int, 0>{});
-
-            // Row energy partials s (I + h) of step k (padded columns have
-            // zero couplings and field, so I + h = 0 there).
-            float psum[MT][4];
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float part = 0.0f;
-#pragma unroll
-                    for (int cw = 0; cw < NCW; ++cw) {
-                        const float ih = acc[mt][cw][j] + h2f[cw];
-                        part += (x[mt][cw][j] >= 0.0f) ? ih : -ih;
-                    }
-                    psum[mt][j] = row_sum16_dpp_f(part);
-                }
-            // lane lr < 8 of each row group adds row (lr >> 2) 16 + 4 lg + (lr & 3)
-            if (lr < 4 * MT) {
-                float t = psum[0][0];
-#pragma unroll
-                for (int u = 1; u < 4 * MT; ++u) t = lr == u ? psum[u >> 2][u & 3] : t;
-                atomicAdd(sE + r3 * 32 + (lr >> 2) * 16 + 4 * lg + (lr & 3), t);
-            }
-            r3 = r3n;
+            uint32_t w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, sg[c][0], sg[c][1], 1.0f, 0);
+            w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, sg[c][2], sg[c][3], 1.0f, 1);
+            *reinterpret_cast<uint16_t*>(srow0 + cbt(c) * 8u) = static_cast<uint16_t>(w);
         }
-
-        // Final state and records of the item.
+    };
+    // P: field J s + h on matrix cores (accumulation starts from h; operand k
+    // order: FP4 nibble t of lane group g is k = 32 g + t for both operands),
+    // then the energy terms s (I + h) (padded columns have I = h = 0) summed
+    // over the replica's four lanes and the waves.
+    auto products = [&](int k) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int c = 0; c < NC; ++c)
+            I[c] = sH[cbt(c) * 4];
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+            const v4i b = *reinterpret_cast<const v4i*>(brow + kb * 64);
+            const v8i B = v8i{b[0], b[1], b[2], b[3], 0, 0, 0, 0};
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                    const v4i j4 = *reinterpret_cast<const v4i*>(jl + (cbt(c) * NKB + kb) * 1024);
+                I[c] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                    v8i{j4[0], j4[1], j4[2], j4[3], 0, 0, 0, 0}, B, I[c], 4, 4, 0, 127, 0, 127);
+            }
+        }
+        float part = 0.0f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const v4f h = sH[cbt(c) * 4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part = __builtin_fmaf(sg[c][j], I[c][j] + h[j], part);
+        }
+        uint32_t c0 = f_to_bits(part), c1 = c0;
+        swap32(c0, c1);
+        c0 = c1 = f_to_bits(bits_to_f(c0) + bits_to_f(c1));
+        swap16(c0, c1);
+        const float tot = bits_to_f(c0) + bits_to_f(c1);
+        if (lg == 0) atomicAdd(sE + (k & 1) * 16 + lr, tot);
+    };
+    // V: records of step k (App. B, Table 3, state 5), the kick, and the
+    // drift of step k + 1.  Every lane that holds the replica takes the same
+    // decision; late in an anneal few steps improve a record, so the updates
+    // run only when some replica of the wave improved (uniform branch).
+    auto update = [&](int k, float ck_s) {
+        const float E = -0.5f * sE[(k & 1) * 16 + lr];  // the sum is even: exact
+        if (tw == 0 && lg == 0) sE[((k + 1) & 1) * 16 + lr] = 0.0f;  // read in the V phase before
+        const float ck = in_vgpr(ck_s);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const float f[4] = {I[c][0], I[c][1], I[c][2], I[c][3]};
+            kick_n<DERIV, 4>(x[c], v[c], f, ck, eps, gamma, sk);
+        }
+        const bool imp = E < bE;
+        if (__any(imp)) {
+            bE = imp ? E : bE;
+            bK = imp ? k : bK;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                    const uint32_t w = *reinterpret_cast<const uint16_t*>(srow0 + cbt(c) * 8u);
+                bp[c] = imp ? w : bp[c];
+            }
+        }
+        if (k + 1 < nsteps) drift(k + 1);
+    };
+
+    drift(0);
+    __syncthreads();
+    if (team == 1) __syncthreads();  // one phase behind
+    for (int k = 0; k < nsteps; ++k) {
+        const float ck = ctab[k];
+        products(k);
+        __syncthreads();
+        update(k, ck);
+        __syncthreads();
+    }
+    if (team == 0) __syncthreads();
+
+    // Final state and records of the item.
+    if (rok) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (!((rmask >> (mt * 4 + j)) & 1u)) continue;
-                const int64_t gr = rb0 + mt * 16 + 4 * lg + j;
-#pragma unroll
-                for (int cw = 0; cw < NCW; ++cw) {
-                    const int64_t idx = gr * Np + col[cw];
-                    a.x[idx] = x[mt][cw][j];
-                    a.v[idx] = v[mt][cw][j];
-                    if (creal[cw]) a.bestS[idx] = ((bestbits >> ((mt * NCW + cw) * 4 + j)) & 1u) ? 1 : -1;
+                const int col = cbt(c) * 16 + col_of(lg, j);
+                if (col < Np) {
+                    a.x[gr * Np + col] = x[c][j];
+                    a.v[gr * Np + col] = v[c][j];
                 }
-                if (wave == 0 && lr == 0) {
-                    a.bestE[gr] = bE[mt][j] == __builtin_inff() ? INT64_MAX : static_cast<int64_t>(bE[mt][j]);
-                    a.bestStep[gr] = bK[mt][j];
-                }
+                if (col < N) a.bestS[gr * Np + col] = ((bp[c] >> (4 * j)) & 8u) ? -1 : 1;
             }
+        }
+        if (tw == 0 && lg == 0) {
+            a.bestE[gr] = bE == __builtin_inff() ? INT64_MAX : static_cast<int64_t>(bE);
+            a.bestStep[gr] = bK;
+        }
     }
 }
 
-__global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(2)))
-k_batch_fp4(const BatchInst* __restrict__ insts, const BatchItem* __restrict__ items, int nitems, int* queue,
-            uint32_t lds_bytes)
+__device__ __forceinline__ uint32_t* squad_counter(unsigned char* lds)
+{
+    return reinterpret_cast<uint32_t*>(lds + 3 * 32 * 4 + 16);
+}
+
+// A barrier of one squad's eight waves: a monotonic LDS counter.  LDS
+// accesses of a wave take effect in order, so every access before the
+// barrier precedes the wave's count.  All eight waves of a squad run the same
+// sequence of barriers, so every wait ends.
+__device__ __forceinline__ void squad_barrier(uint32_t* counter, uint32_t& target, int lane)
+{
+    target += kSquad;
+    if (lane == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    while (static_cast<int32_t>(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) - target) < 0)
+        __builtin_amdgcn_s_sleep(0);
+    __atomic_signal_fence(__ATOMIC_ACQ_REL);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// The steps of one work item for one squad of eight waves, for instances whose
+// couplings leave room for two in LDS: each squad takes items of its own, so
+// that one squad's waits (operand reads, products, its one barrier per step)
+// are the other's VALU time.  A wave owns NF column blocks of both replica
+// halves and, with HALF, one more of the half sw / 4 (ncb = 8 NF + 4), so all
+// waves carry the same number of tiles.
+// Returns the barrier count it reached.
+template <int NF, bool HALF, int DERIV>
+__device__ __attribute__((noinline)) uint32_t squad_item(const BatchInst* ap, int blk, LdsByte* lds3,
+                                                         uint32_t target, int sw, int lane)
+{
+    unsigned char* const lds = (unsigned char*)lds3;
+    uint32_t* counter = squad_counter(lds);
+    constexpr int NC = NF + (HALF ? 1 : 0);  // column blocks of the wave = k blocks of 128
+    constexpr int NT = 2 * NF + (HALF ? 1 : 0);
+    constexpr uint32_t srow = NC * 64u + 16u;
+    constexpr uint32_t sb = kBatchRows * srow;
+    constexpr uint32_t jb = (8u * NF + (HALF ? 4u : 0u)) * NC * 1024u;
+    sw = __builtin_amdgcn_readfirstlane(sw);
+    blk = __builtin_amdgcn_readfirstlane(blk);
+    const BatchInst& a = *uniform_ptr(ap);
+    const int Np = __builtin_amdgcn_readfirstlane(a.Np), N = __builtin_amdgcn_readfirstlane(a.N);
+    float* sE = reinterpret_cast<float*>(lds);  // [3][32] row energy sums of steps k mod 3 (exact integers)
+    unsigned char* sJ = lds + kFixedLds;
+    unsigned char* sS = sJ + jb;  // [2][32][srow] FP4 spins by step parity
+    const int nsteps = __builtin_amdgcn_readfirstlane(static_cast<int>(a.k1));
+    const int lr = lane & 15, lg = lane >> 4;
+    const v4f* sH = reinterpret_cast<const v4f*>(sS + 2u * sb) + lg;  // fields of the lane's columns of block 0
+    const uint64_t seed = *a.seed;
+    const int mth = sw >> 2;  // replica half of the HALF tile
+    // tile t: column block cbt(cw(t)), replica half mtt(t)
+    auto cwt = [&](int t) { return t < 2 * NF ? t >> 1 : NF; };
+    auto mtt = [&](int t) { return t < 2 * NF ? (t & 1) : mth; };
+    auto cbt = [&](int cw) { return cw < NF ? sw + kSquad * cw : kSquad * NF + (sw & 3); };
+    const int64_t gr0 = static_cast<int64_t>(blk) * kBatchRows + lr;  // replica of half 0; gr0 + 16 in half 1
+    const bool rok[2] = {gr0 < a.R, gr0 + 16 < a.R};
+    float x[NT][4], v[NT][4];
+    float bE[2] = {__builtin_inff(), __builtin_inff()};  // record energies of the two replicas (+inf: none yet)
+    int32_t bK[2] = {-1, -1};
+    uint32_t bp[NT];  // record spins: the four FP4 codes of each tile
+    // draws of a generator round into y (all tiles; 0 in padding)
+    auto draw = [&](uint32_t tag, uint64_t round, float (&y)[NT][4]) {
+#pragma unroll
+        for (int cw = 0; cw < NC; ++cw) {
+            const uint64_t c8 = static_cast<uint64_t>(cbt(cw)) * 2 + (lg >> 1);
+            const auto real = [&](int j) { return cbt(cw) * 16 + col_of(lg, j) < N; };
+            if (cw < NF) {
+                const Draws8 d = draws_both(seed, tag, static_cast<uint64_t>(gr0), round, c8, lg & 1);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    y[2 * cw][j] = (real(j) && rok[0]) ? d.a[j] : 0.0f;
+                    y[2 * cw + 1][j] = (real(j) && rok[1]) ? d.b[j] : 0.0f;
+                }
+            } else {
+                const Draws4 d = draws_one(seed, tag, static_cast<uint64_t>(gr0) + 16 * mth, round, c8, lg & 1);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) y[NT - 1][j] = (real(j) && (mth ? rok[1] : rok[0])) ? d.g[j] : 0.0f;
+            }
+        }
+    };
+    draw(kTagX, 0, x);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        bp[t] = 0x2222u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[t][j] = 0.0f;
+    }
+    const float eps = in_vgpr(a.eps), gamma = in_vgpr(a.gamma);
+    Sech2K sk{};
+    if constexpr (DERIV == 0) sk = sech2_in_vgprs();
+    const int L = static_cast<int>(a.L < INT32_MAX ? a.L : INT32_MAX);
+    const ConstF ctab = scalar_table(a.ctab);
+    int next_ref = 0, round = 0;
+    // the lane's byte offset in a spin buffer: row lr, its codes of column block 0
+    const uint32_t soff = static_cast<uint32_t>(lr) * srow + 2u * lg;
+    const unsigned char* jl =
+        sJ + ((lane & 48) + 8 * (lr >> 3) + 2 * ((lr >> 2) & 1) + ((lr >> 1) & 1) + 4 * (lr & 1)) * 16;
+
+    // Records of step kp (App. B, Table 3, state 5), whose spins are in the
+    // buffer `pv`: every lane that holds a replica takes the same decision.
+    // Late in an anneal few steps improve a record: the updates run only when
+    // some replica of the wave improved (uniform branch).  The wave's own
+    // codes of the step are still in their buffer.
+    auto records = [&](int r3p, const unsigned char* pv, int kp) {
+        const float E0 = -0.5f * sE[r3p * 32 + lr], E1 = -0.5f * sE[r3p * 32 + 16 + lr];  // the sums are even: exact
+        const bool i0 = E0 < bE[0], i1 = E1 < bE[1];
+        if (__any(i0 || i1)) {
+            bE[0] = i0 ? E0 : bE[0];
+            bE[1] = i1 ? E1 : bE[1];
+            bK[0] = i0 ? kp : bK[0];
+            bK[1] = i1 ? kp : bK[1];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const uint32_t w =
+                    *reinterpret_cast<const uint16_t*>(pv + soff + mtt(t) * 16u * srow + cbt(cwt(t)) * 8u);
+                bp[t] = (mtt(t) ? i1 : i0) ? w : bp[t];
+            }
+        }
+    };
+
+    int r3 = 0;
+    for (int k = 0; k < nsteps; ++k) {
+        const int r3p = (r3 == 0) ? 2 : r3 - 1, r3n = (r3 == 2) ? 0 : r3 + 1;
+        unsigned char* S = sS + (k & 1) * sb;
+        const float ck_s = ctab[k];
+        if (k == next_ref) {  // momentum refresh
+            draw(kTagV, static_cast<uint64_t>(round), v);
+            ++round;
+            next_ref = L > INT32_MAX - k ? INT32_MAX : k + L;
+        }
+        // Drift and readout; the spins go to LDS for the product.
+        float sg[NT][4];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                x[t][j] = __builtin_fmaf(eps, v[t][j], x[t][j]);
+                sg[t][j] = x[t][j] >= 0.0f ? 1.0f : -1.0f;
+            }
+            uint32_t w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, sg[t][0], sg[t][1], 1.0f, 0);
+            w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, sg[t][2], sg[t][3], 1.0f, 1);
+            *reinterpret_cast<uint16_t*>(S + soff + mtt(t) * 16u * srow + cbt(cwt(t)) * 8u) = static_cast<uint16_t>(w);
+        }
+        squad_barrier(counter, target, lane);  // spins of step k and energy sums of step k - 1 complete
+        if (k > 0) records(r3p, sS + ((k + 1) & 1) * sb, k - 1);
+        if (sw == 0 && lane < 32) sE[r3n * 32 + lane] = 0.0f;  // read two steps ago
+
+        // Field J s + h on matrix cores, as in team_item.
+        v4f I[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) I[t] = sH[cbt(cwt(t)) * 4];
+        const unsigned char* brow = S + lr * srow + 16 * lg;
+#pragma unroll
+        for (int kb = 0; kb < NC; ++kb) {
+            v8i B[2], Bh;
+            if constexpr (NF > 0) {
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const v4i b = *reinterpret_cast<const v4i*>(brow + m * 16 * srow + kb * 64);
+                    B[m] = v8i{b[0], b[1], b[2], b[3], 0, 0, 0, 0};
+                }
+            }
+            if constexpr (HALF) {
+                const v4i b = *reinterpret_cast<const v4i*>(brow + mth * 16 * srow + kb * 64);
+                Bh = v8i{b[0], b[1], b[2], b[3], 0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int cw = 0; cw < NC; ++cw) {
+                const v4i j4 = *reinterpret_cast<const v4i*>(jl + (cbt(cw) * NC + kb) * 1024);
+                const v8i A = v8i{j4[0], j4[1], j4[2], j4[3], 0, 0, 0, 0};
+                if (cw < NF) {
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+                        I[2 * cw + m] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B[m], I[2 * cw + m], 4, 4,
+                                                                                         0, 127, 0, 127);
+                } else {
+                    I[NT - 1] =
+                        __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, Bh, I[NT - 1], 4, 4, 0, 127, 0, 127);
+                }
+            }
+        }
+        // Energy partials s (I + h) of the step, summed over the four lanes of
+        // each replica: after the 32-lane swap the lower lanes hold half 0
+        // and the upper lanes half 1.
+        {
+            float part[2] = {0.0f, 0.0f}, ph = 0.0f;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const v4f h = sH[cbt(cwt(t)) * 4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float ih = I[t][j] + h[j];
+                    if (t < 2 * NF)
+                        part[t & 1] = __builtin_fmaf(sg[t][j], ih, part[t & 1]);
+                    else
+                        ph = __builtin_fmaf(sg[t][j], ih, ph);
+                }
+            }
+            if constexpr (HALF) {
+                part[0] += mth ? 0.0f : ph;
+                part[1] += mth ? ph : 0.0f;
+            }
+            uint32_t p0 = f_to_bits(part[0]), p1 = f_to_bits(part[1]);
+            swap32(p0, p1);
+            uint32_t c0 = f_to_bits(bits_to_f(p0) + bits_to_f(p1)), c1 = c0;
+            swap16(c0, c1);
+            const float tot = bits_to_f(c0) + bits_to_f(c1);
+            if ((lg & 1) == 0) atomicAdd(sE + r3 * 32 + (lg >> 1) * 16 + lr, tot);
+        }
+        const float ck = in_vgpr(ck_s);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const float f[4] = {I[t][0], I[t][1], I[t][2], I[t][3]};
+            kick_n<DERIV, 4>(x[t], v[t], f, ck, eps, gamma, sk);
+        }
+        r3 = r3n;
+    }
+    squad_barrier(counter, target, lane);  // energy sums of the last step complete
+    records((r3 == 0) ? 2 : r3 - 1, sS + ((nsteps + 1) & 1) * sb, nsteps - 1);
+
+    // Final state and records of the item.
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        if (!(mtt(t) ? rok[1] : rok[0])) continue;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int col = cbt(cwt(t)) * 16 + col_of(lg, j);
+            const int64_t idx = (gr0 + 16 * mtt(t)) * Np + col;
+            a.x[idx] = x[t][j];
+            a.v[idx] = v[t][j];
+            if (col < N) a.bestS[idx] = ((bp[t] >> (4 * j)) & 8u) ? -1 : 1;
+        }
+    }
+    if (sw == 0 && lg < 2 && (lg ? rok[1] : rok[0])) {
+        const int64_t gr = gr0 + 16 * lg;
+        const float e = lg ? bE[1] : bE[0];
+        a.bestE[gr] = e == __builtin_inff() ? INT64_MAX : static_cast<int64_t>(e);
+        a.bestStep[gr] = lg ? bK[1] : bK[0];
+    }
+    return target;
+}
+
+// Couplings, fields and cleared spins of one item into `lds` by nthr threads
+// (column blocks up to ncb_pad and k positions past Np are zero; spins there
+// must hold a finite value).
+__device__ __forceinline__ void stage_item(const BatchInst* ap, unsigned char* lds, int ncb_pad, uint32_t sbytes, int t,
+                                           int nthr)
+{
+    const int Np = ap->Np, nkb = nkb4_of(Np);
+    const uint32_t n = static_cast<uint32_t>(Np / 16) * nkb * 64u, npad = static_cast<uint32_t>(ncb_pad) * nkb * 64u;
+    const uint4* src = reinterpret_cast<const uint4*>(ap->J4);
+    uint4* dst = reinterpret_cast<uint4*>(lds + kFixedLds);
+    for (uint32_t u = t; u < npad; u += nthr) dst[u] = u < n ? src[u] : uint4{0u, 0u, 0u, 0u};
+    uint32_t* sz = reinterpret_cast<uint32_t*>(lds + kFixedLds + npad * 16u);
+    for (uint32_t u = t; u < sbytes / 4u; u += nthr) sz[u] = 0u;
+    // fields in the order of the lanes' columns
+    float* sh = reinterpret_cast<float*>(lds + kFixedLds + npad * 16u + sbytes);
+    for (int u = t; u < ncb_pad * 16; u += nthr) {
+        const int col = (u & ~15) + col_of((u >> 2) & 3, u & 3);
+        sh[u] = col < Np ? static_cast<float>(ap->h[col]) : 0.0f;
+    }
+    if (t < 96) reinterpret_cast<int32_t*>(lds)[t] = 0;
+}
+
+template <int NC>
+__device__ __forceinline__ void team_item_d(const BatchInst* a, int blk, LdsByte* lds, int wave, int lane)
+{
+    if (a->deriv)
+        team_item<NC, 1>(a, blk, lds, wave, lane);
+    else
+        team_item<NC, 0>(a, blk, lds, wave, lane);
+}
+
+template <int NF, bool HALF>
+__device__ __forceinline__ uint32_t squad_item_d(const BatchInst* a, int blk, LdsByte* lds, uint32_t target,
+                                                 int sw, int lane)
+{
+    return a->deriv ? squad_item<NF, HALF, 1>(a, blk, lds, target, sw, lane)
+                    : squad_item<NF, HALF, 0>(a, blk, lds, target, sw, lane);
+}
+
+// Every workgroup first takes the items for teams (all sixteen waves on one),
+// then its two squads take the others independently; both queues are sorted
+// largest first.  A workgroup's first items are given by its index (team item
+// b to workgroup b; of the workgroups without one, squad items to the first
+// squads before the second ones), later ones come from the queue counters.
+__global__ void __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4)))
+k_batch_fp4(const BatchInst* __restrict__ insts, const BatchItem* __restrict__ items, int nteam, int nsquad,
+            int* queue, uint32_t squad_lds)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grid = static_cast<int>(gridDim.x), b = static_cast<int>(blockIdx.x);
     int* sItem = reinterpret_cast<int*>(lds + 3 * 32 * 4);
-    for (;;) {
+    for (int q = b; q < nteam;) {
+        const BatchItem it = items[q];
+        const BatchInst* ap = insts + it.inst;
+        const int nc = nkb4_of(ap->Np);
+        stage_item(ap, lds, 8 * nc, 32u * (64u * nc + 16u), tid, kBT);
+        __syncthreads();
+        switch (nc) {
+        case 1: team_item_d<1>(ap, it.block, (LdsByte*)lds, wave, lane); break;
+        case 2: team_item_d<2>(ap, it.block, (LdsByte*)lds, wave, lane); break;
+        case 3: team_item_d<3>(ap, it.block, (LdsByte*)lds, wave, lane); break;
+        default: team_item_d<4>(ap, it.block, (LdsByte*)lds, wave, lane); break;
+        }
+        __syncthreads();
         if (tid == 0) *sItem = atomicAdd(queue, 1);
         __syncthreads();
-        const int q = __builtin_amdgcn_readfirstlane(*sItem);
-        if (q >= nitems) break;
-        const BatchItem it = items[q];
-        const BatchInst a = insts[it.inst];
-        const int Np = a.Np, ncb = Np / 16, nkb = nkb4_of(Np);
-        const uint32_t jb = jbytes_of(Np), sb = sbytes_of(Np);
-        // spins double-buffered when both buffers fit the launch's LDS (else
-        // one buffer and a second barrier per step)
-        const bool dbuf = kFixedLds + jb + 2 * sb <= lds_bytes;
-        // coupling slice into LDS, spins and energy sums cleared (k positions
-        // past Np meet zero couplings but must hold a finite value)
-        {
-            const uint4* src = reinterpret_cast<const uint4*>(a.J4);
-            uint4* dst = reinterpret_cast<uint4*>(lds + kFixedLds);
-            for (uint32_t u = tid; u < jb / 16u; u += kBT) dst[u] = src[u];
-            uint32_t* sz = reinterpret_cast<uint32_t*>(lds + kFixedLds + jb);
-            const uint32_t nsw = (dbuf ? 2u : 1u) * sb / 4u;
-            for (uint32_t u = tid; u < nsw; u += kBT) sz[u] = 0u;
-            if (tid < 96) reinterpret_cast<int32_t*>(lds)[tid] = 0;
+        q = __builtin_amdgcn_readfirstlane(*sItem);
+    }
+    if (nsquad == 0) return;
+    // squads, each with half of the LDS
+    const int squad = wave >> 3, sw = wave & 7, st = tid & (64 * kSquad - 1);
+    unsigned char* base = lds + squad * squad_lds;
+    uint32_t* counter = squad_counter(base);
+    int* slot = reinterpret_cast<int*>(base + 3 * 32 * 4);
+    __syncthreads();
+    if (st == 0) *counter = 0u;
+    __syncthreads();
+    uint32_t target = 0;
+    int q = b < nteam ? -1 : (b - nteam) + (squad ? grid - nteam : 0);
+    for (;;) {
+        if (q < 0) {
+            if (st == 0) *slot = atomicAdd(queue + 1, 1);
+            squad_barrier(counter, target, lane);
+            q = __builtin_amdgcn_readfirstlane(*slot);
         }
-        __syncthreads();
-        const int ncw = wave < ncb ? (ncb - wave + kBW - 1) / kBW : 0;
+        if (q >= nsquad) break;
+        const BatchItem it = items[nteam + q];
+        const BatchInst* ap = insts + it.inst;
+        const int q4 = ap->Np / 64, nkb = nkb4_of(ap->Np);
+        stage_item(ap, base, 4 * q4, 2u * 32u * (64u * nkb + 16u), st, 64 * kSquad);
+        squad_barrier(counter, target, lane);
         const int blk = it.block;
-        // nkb = ceil(ncb / 8); a wave owns nkb or nkb - 1 column blocks
-        if (nkb == 1) {
-            if (ncw == 1) batch_item<1, 1>(a, blk, lds, dbuf, wave, lane);
-            else batch_item<1, 0>(a, blk, lds, dbuf, wave, lane);
-        } else if (nkb == 2) {
-            if (ncw == 2) batch_item<2, 2>(a, blk, lds, dbuf, wave, lane);
-            else batch_item<2, 1>(a, blk, lds, dbuf, wave, lane);
-        } else if (nkb == 3) {
-            if (ncw == 3) batch_item<3, 3>(a, blk, lds, dbuf, wave, lane);
-            else batch_item<3, 2>(a, blk, lds, dbuf, wave, lane);
-        } else {
-            if (ncw == 4) batch_item<4, 4>(a, blk, lds, dbuf, wave, lane);
-            else batch_item<4, 3>(a, blk, lds, dbuf, wave, lane);
+        switch (q4) {
+        case 1: target = squad_item_d<0, true>(ap, blk, (LdsByte*)base, target, sw, lane); break;
+        case 2: target = squad_item_d<1, false>(ap, blk, (LdsByte*)base, target, sw, lane); break;
+        case 3: target = squad_item_d<1, true>(ap, blk, (LdsByte*)base, target, sw, lane); break;
+        default: target = squad_item_d<2, false>(ap, blk, (LdsByte*)base, target, sw, lane); break;
         }
-        __syncthreads();
+        squad_barrier(counter, target, lane);
+        q = -1;
     }
 }
 
-__global__ void k_batch_queue_reset(int* queue)
+// The queues' counters: the first index that no workgroup has by its own.
+__global__ void k_batch_queue_reset(int* queue, int first_team, int first_squad)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *queue = 0;
+    if (threadIdx.x == 0 && blockIdx.x == 0) {
+        queue[0] = first_team;
+        queue[1] = first_squad;
+    }
 }
 
 }  // namespace
 
-size_t batch_fp4_lds_bytes(int Np, bool double_buffered)
+bool batch_fp4_squad(int Np) { return Np <= kSquadMaxNp; }
+
+size_t batch_fp4_lds_bytes(int Np, bool squad)
 {
-    return kFixedLds + jbytes_of(Np) + (double_buffered ? 2u : 1u) * sbytes_of(Np);
+    const uint32_t nkb = static_cast<uint32_t>(nkb4_of(Np));
+    if (!squad)
+        return kFixedLds + 8u * nkb * nkb * 1024u + 32u * (64u * nkb + 16u) + 4u * 128u * nkb;
+    return kFixedLds + static_cast<uint32_t>(Np / 16) * nkb * 1024u + 2u * 32u * (64u * nkb + 16u) +
+           4u * static_cast<uint32_t>(Np);
 }
 
-hipError_t launch_batch_queue_reset(int* queue, hipStream_t st)
+static size_t launch_lds(size_t team_lds, size_t squad_lds)
 {
-    hipLaunchKernelGGL(k_batch_queue_reset, dim3(1), dim3(64), 0, st, queue);
-    return hipGetLastError();
+    return std::max(team_lds, 2 * ((squad_lds + 255) & ~static_cast<size_t>(255)));
 }
 
-int batch_fp4_grid(size_t lds)
+int batch_fp4_grid(size_t team_lds, size_t squad_lds)
 {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    const size_t lds = launch_lds(team_lds, squad_lds);
     const void* f = reinterpret_cast<const void*>(k_batch_fp4);
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
         return 0;
@@ -444,14 +748,20 @@ int batch_fp4_grid(size_t lds)
     return per * cus;
 }
 
-hipError_t launch_batch_fp4(const BatchInst* insts, const BatchItem* items, int nitems, int* queue, size_t lds,
-                            hipStream_t st)
+hipError_t launch_batch_fp4(const BatchInst* insts, const BatchItem* items, int nteam, int nsquad, int* queue,
+                            size_t team_lds, size_t squad_lds, hipStream_t st)
 {
-    const int grid = batch_fp4_grid(lds);
+    const int grid = batch_fp4_grid(team_lds, squad_lds);
     if (grid < 1) return hipErrorInvalidConfiguration;
-    const int nwg = grid < nitems ? grid : (nitems > 0 ? nitems : 1);
-    hipLaunchKernelGGL(k_batch_fp4, dim3(static_cast<unsigned>(nwg)), dim3(kBT), lds, st, insts, items, nitems, queue,
-                       static_cast<uint32_t>(lds));
+    const int want = std::max(1, nteam + nsquad);
+    const int nwg = grid < want ? grid : want;
+    const int first_team = std::min(nteam, nwg), first_squad = nteam < nwg ? 2 * (nwg - nteam) : 0;
+    hipLaunchKernelGGL(k_batch_queue_reset, dim3(1), dim3(64), 0, st, queue, first_team, first_squad);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_batch_fp4, dim3(static_cast<unsigned>(nwg)), dim3(kBT), launch_lds(team_lds, squad_lds), st,
+                       insts, items, nteam, nsquad, queue,
+                       static_cast<uint32_t>((squad_lds + 255) & ~static_cast<size_t>(255)));
     return hipGetLastError();
 }
 

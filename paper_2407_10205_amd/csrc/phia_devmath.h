@@ -16,7 +16,7 @@
 //    series of sin to theta^9 and cos to theta^10, rotation by k quarter turns.
 //  * sech^2(u) = 4 e^{-2|u|} / (1 + e^{-2|u|})^2, the factor
 //    d tanh(gamma x)/dx / gamma of Eq. 8, with the reciprocal of 1 + e^{-2|u|}
-//    from a linear start and three Newton steps (no division).
+//    from a quadratic start and two Newton steps (no division).
 //  * Gaussians: Philox4x64-10 (Salmon et al., SC'11) keyed by (seed, 0) at
 //    counter (i/8, round, replica, tag); word pair (i mod 8)/2 of the output
 //    feeds a Box-Muller transform, cosine for even i, sine for odd i.
@@ -104,8 +104,6 @@ PHIA_DEV void dev_sincos_2pi(float u, float& c, float& s)
     s = (q == 0) ? sn : (q == 1) ? cs : (q == 2) ? -sn : -cs;
 }
 
-// 1/(1+t) for t in (0, 1]: the line 24/17 - 8q/17 (relative error <= 1/17
-// on q in [1, 2]) refined by three Newton steps y += y (1 - q y).
 // sech^2 u = 4t / (1 + t)^2, t = e^{-2|u|}: the argument clamped at -80
 // (so 4t stays normal), 4t from the exponential's sequence with the Taylor
 // coefficients times 4 and ldexp as the scale, 1/(1 + t) from a quadratic
@@ -134,6 +132,83 @@ PHIA_DEV float dev_sech2(float u)
         z = __builtin_fmaf(z, e, z);
     }
     return t4 * (z * z);
+}
+
+// A value held in a VGPR from here on.  FP32 add, mul and fma whose operands
+// are all VGPRs (or inline constants) issue in 2 cycles per wave on gfx950,
+// with one SGPR operand in 4 (measured with two or more waves per SIMD: 2.1
+// to 2.6 against 4.2 cycles).  The compiler puts loop constants and kernel
+// arguments into SGPRs, which is right for sweeps that wait on something
+// else (and need the registers); a sweep bound by VALU issue moves the
+// constants of its kick here.
+PHIA_DEV float in_vgpr(float c)
+{
+    asm volatile("" : "+v"(c));
+    return c;
+}
+
+// Constants of dev_sech2_n.
+struct Sech2K {
+    float m2log2e = -2.0f * kLog2e, magic = 0x1.8p23f, ln2hi_h = 0.5f * kLn2Hi, ln2lo_h = 0.5f * kLn2Lo,
+          c7 = 128.0f * (4.0f / 5040.0f), c6 = 64.0f * (4.0f / 720.0f), c5 = 32.0f * (4.0f / 120.0f),
+          c4 = 16.0f * (4.0f / 24.0f), c3 = 8.0f * (4.0f / 6.0f), eight = 8.0f, quarter = 0.25f, z2 = 32.0f / 99.0f,
+          z1 = -144.0f / 99.0f, z0 = 210.0f / 99.0f;
+};
+
+// The same in VGPRs.
+PHIA_DEV Sech2K sech2_in_vgprs()
+{
+    const Sech2K c;
+    return Sech2K{in_vgpr(c.m2log2e), in_vgpr(c.magic), in_vgpr(c.ln2hi_h), in_vgpr(c.ln2lo_h), in_vgpr(c.c7),
+                  in_vgpr(c.c6),      in_vgpr(c.c5),    in_vgpr(c.c4),      in_vgpr(c.c3),      in_vgpr(c.eight),
+                  in_vgpr(c.quarter), in_vgpr(c.z2),    in_vgpr(c.z1),      in_vgpr(c.z0)};
+}
+
+// dev_sech2 of n arguments for sweeps bound by VALU issue: the same sequence
+// evaluated on half the argument.  With y = -2 min(|u|, 40) and r = y - k ln2,
+// every step here holds r / 2 (from |u| directly, which saves the doubling)
+// and 2^i times the i-th Horner value (coefficients times 2^i), exact powers
+// of two of the values of dev_sech2, so each result is the same to the last
+// bit.  k = rint(-2 log2e |u|) comes from
+// adding and subtracting 1.5 2^23 (round to nearest even at unit spacing;
+// |k| <= 116), and since the low bits of that sum hold k, one shift-and-add
+// puts k into the exponent of the normal p: two 2-cycle additions and one
+// 4-cycle operation where v_rndne, v_cvt_i32 and v_ldexp take 4 cycles each.
+// With the constants in SGPRs it gains nothing (the interleaved sweep took
+// 6.08 against 5.56 ms on 2000 steps of max-cut N = 800 with it).
+//
+// n arguments advance together, one operation of each at a time: a wave that
+// issues one dependent operation after the other waits about 2 more cycles
+// per operation (5.9 against 4.4 cycles with one wave per SIMD).
+template <int n>
+PHIA_DEV void dev_sech2_n(const float (&u)[n], float (&d)[n], const Sech2K& c)
+{
+    float a[n], t[n], r[n], p[n], q[n], z[n];
+#define PHIA_EACH _Pragma("unroll") for (int i = 0; i < n; ++i)
+    PHIA_EACH a[i] = __builtin_fminf(__builtin_fabsf(u[i]), 40.0f);
+    PHIA_EACH t[i] = a[i] * c.m2log2e;
+    PHIA_EACH t[i] = t[i] + c.magic;
+    PHIA_EACH p[i] = t[i] - c.magic;  // k
+    PHIA_EACH r[i] = __builtin_fmaf(-p[i], c.ln2hi_h, -a[i]);
+    PHIA_EACH r[i] = __builtin_fmaf(-p[i], c.ln2lo_h, r[i]);
+    PHIA_EACH p[i] = __builtin_fmaf(c.c7, r[i], c.c6);
+    PHIA_EACH p[i] = __builtin_fmaf(p[i], r[i], c.c5);
+    PHIA_EACH p[i] = __builtin_fmaf(p[i], r[i], c.c4);
+    PHIA_EACH p[i] = __builtin_fmaf(p[i], r[i], c.c3);
+    PHIA_EACH p[i] = __builtin_fmaf(p[i], r[i], c.eight);
+    PHIA_EACH p[i] = __builtin_fmaf(p[i], r[i], c.eight);
+    PHIA_EACH p[i] = __builtin_fmaf(p[i], r[i], 4.0f);
+    PHIA_EACH t[i] = bits_to_f((f_to_bits(t[i]) << 23) + f_to_bits(p[i]));  // 4 e^y
+    PHIA_EACH q[i] = __builtin_fmaf(t[i], c.quarter, 1.0f);
+    PHIA_EACH z[i] = __builtin_fmaf(c.z2, q[i], c.z1);
+    PHIA_EACH z[i] = __builtin_fmaf(z[i], q[i], c.z0);
+    PHIA_EACH r[i] = __builtin_fmaf(-q[i], z[i], 1.0f);
+    PHIA_EACH z[i] = __builtin_fmaf(z[i], r[i], z[i]);
+    PHIA_EACH r[i] = __builtin_fmaf(-q[i], z[i], 1.0f);
+    PHIA_EACH z[i] = __builtin_fmaf(z[i], r[i], z[i]);
+    PHIA_EACH z[i] = z[i] * z[i];
+    PHIA_EACH d[i] = t[i] * z[i];
+#undef PHIA_EACH
 }
 
 // POLY2 mode: max(0, 1 - u^2 / 2.25) in place of sech^2 (t = u*u,

@@ -87,36 +87,27 @@ __device__ __forceinline__ float kick_tf(float x, float v, float If, float ck, f
     return __builtin_fmaf(eps, g, v);
 }
 
-// row_sum16_dpp for FP32 values that are integers below 2^24 in magnitude
-// (every partial sum is then exact, so the order does not matter).
-__device__ __forceinline__ float dpp_f_b1(float a)
+// The kick of n elements for sweeps bound by VALU issue, one operation of
+// each at a time; ck, eps, gamma and the constants in VGPRs (in_vgpr).
+template <int DERIV, int n>
+__device__ __forceinline__ void kick_n(const float (&x)[n], float (&v)[n], const float (&If)[n], float ck, float eps,
+                                       float gamma, const Sech2K& sk)
 {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a), 0xb1, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float dpp_f_4e(float a)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a), 0x4e, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float dpp_f_141(float a)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a), 0x141, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float row_sum16_dpp_f(float v)
-{
-    v += dpp_f_b1(v);   // quad_perm [1,0,3,2]
-    v += dpp_f_4e(v);   // quad_perm [2,3,0,1]
-    v += dpp_f_141(v);  // row_half_mirror
-    v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xf, 0xf, true));
-    return v;
-}
-
-__device__ __forceinline__ float kick(float x, float v, int I, float ck, float eps, float gamma, int deriv)
-{
-    const float u = gamma * x;
-    const float d = deriv ? dev_poly2(u) : dev_sech2(u);
-    const float p = ck * d;
-    const float g = __builtin_fmaf(p, static_cast<float>(I), -x);
-    return __builtin_fmaf(eps, g, v);
+    float u[n], d[n];
+#pragma unroll
+    for (int i = 0; i < n; ++i) u[i] = gamma * x[i];
+    if constexpr (DERIV) {
+#pragma unroll
+        for (int i = 0; i < n; ++i) d[i] = dev_poly2(u[i]);
+    } else {
+        dev_sech2_n<n>(u, d, sk);
+    }
+#pragma unroll
+    for (int i = 0; i < n; ++i) d[i] = ck * d[i];
+#pragma unroll
+    for (int i = 0; i < n; ++i) d[i] = __builtin_fmaf(d[i], If[i], -x[i]);
+#pragma unroll
+    for (int i = 0; i < n; ++i) v[i] = __builtin_fmaf(eps, d[i], v[i]);
 }
 
 // Sum over the 16 lanes of a DPP row (lanes sharing lane / 16), result in

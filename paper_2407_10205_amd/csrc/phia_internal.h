@@ -126,13 +126,11 @@ struct BatchInst {
     int64_t* bestE;             // [R]
     int8_t* bestS;              // [R][Np]
     int64_t* bestStep;          // [R]
-    int64_t k0, k1;             // steps [k0, k1) of this launch
+    int64_t k1;                 // steps [0, k1), from x ~ N(0, I), v = 0 and no records
     int64_t L;                  // momentum refresh period
     float eps, gamma;
     int32_t N, Np, R;
     int32_t deriv;              // 0: sech^2, 1: POLY2
-    int32_t init;               // 1: draw x ~ N(0, I), v = 0 and reset the records first (k0 = 0)
-    int32_t pad_;
 };
 struct BatchItem {
     int32_t inst;               // index into the instance table
@@ -140,13 +138,17 @@ struct BatchItem {
 };
 constexpr int kBatchRows = 32;           // replicas per work item
 constexpr int kBatchFp4MaxNp = 512;      // columns of the persistent sweep (8 waves x 4 column blocks)
-// LDS the persistent sweep needs for an instance of Np columns (J slice and
-// spins double-buffered, or single-buffered when double does not fit).
-size_t batch_fp4_lds_bytes(int Np, bool double_buffered);
-hipError_t launch_batch_fp4(const BatchInst* insts, const BatchItem* items, int nitems, int* queue, size_t lds,
-                            hipStream_t st);
-hipError_t launch_batch_queue_reset(int* queue, hipStream_t st);
-int batch_fp4_grid(size_t lds);
+// An item of the persistent sweep is run by a whole workgroup (two teams) or,
+// for instances small enough (batch_fp4_squad), by half of one (a squad), two
+// at a time.  LDS of one instance of Np columns in either form.
+bool batch_fp4_squad(int Np);
+size_t batch_fp4_lds_bytes(int Np, bool squad);
+// items: nteam for whole workgroups, then nsquad for squads, each sorted
+// largest first; team_lds, squad_lds: the largest batch_fp4_lds_bytes of
+// either (0: none).  queue: 2 counters, set by the launch.
+hipError_t launch_batch_fp4(const BatchInst* insts, const BatchItem* items, int nteam, int nsquad, int* queue,
+                            size_t team_lds, size_t squad_lds, hipStream_t st);
+int batch_fp4_grid(size_t team_lds, size_t squad_lds);
 size_t sweep_batch_lds_bytes(int path, int Np, int j_lds, int mh);
 hipError_t prepare_sweep_batch(int path, int cbw, int mh, size_t lds_bytes);
 hipError_t launch_sweep_batch(int path, int cbw, int mh, const SweepArgs* dtable, int nitems, size_t lds_bytes,
