@@ -238,6 +238,7 @@ phia_status launch_group_chunk(phia_problem* const* probs, int count, const int6
         for (int i : L.members)
             if (probs[i]->give_up && (e = hipMemsetAsync(probs[i]->derr, 0x02, 1, st)) != hipSuccess)
                 return hip_fail(probs[i], e, "error word");
+        for (int i : L.members) probs[i]->err_live = true;
         if ((e = launch_sweep_group_table(L.path, L.mt, L.cbw, L.mh, dtab + offs[li], L.nwg, L.lds, st)) !=
             hipSuccess)
             return hip_fail(nullptr, e, "group table launch");

@@ -47,7 +47,7 @@ struct SweepArgs {
     int32_t xcd_map;            // 1: group members share blockIdx % 8
     int32_t j_lds;              // 1: J slice resident in LDS, 0: read from global
     int32_t inc;                // 1: flip-incremental field update (column split, J streamed)
-    int64_t* incstat;           // [3] incremental steps, full-product steps, k blocks of the
+    int64_t* incstat;           // [4], the init kernel clears it: incremental steps, full-product steps, k blocks of the
                                 //     incremental products (member 0 of every group), or null
     // group exchange (G > 1)
     uint64_t* xbits;            // [2][ngroups][rows][Np/16] tagged sign words
@@ -94,7 +94,9 @@ bool valu_variant(int form, int rb, int mh, bool jl);  // a compiled (form, rows
 hipError_t launch_sweep_valu(int form, int rb, bool jl, const SweepArgs& a, hipStream_t st);
 hipError_t launch_sweep_mfma(int path, int mt, int cbw, const SweepArgs& a, size_t lds_bytes, hipStream_t st);
 size_t sweep_mfma_lds_bytes(int path, int mt, const SweepArgs& a);
-hipError_t launch_argmin(const int64_t* bestE, int32_t R, int64_t* out2, hipStream_t st);
+// out: (energy, replica, *err or 0), then with bestS the winner's n spins at byte 64
+hipError_t launch_argmin(const int64_t* bestE, int32_t R, int64_t* out, hipStream_t st,
+                         const int8_t* bestS = nullptr, int32_t Np = 0, int32_t n = 0, const int32_t* err = nullptr);
 // n problems' argmins in one launch (phia_server_kernels.hip): pairs[2 j], pairs[2 j + 1] =
 // (energy, replica) of problem j, errs[j] = *err[j] (0 for a null err[j]).
 hipError_t launch_argmin_many(const int64_t* const* bestE, const int32_t* R, const int32_t* const* err, int n,

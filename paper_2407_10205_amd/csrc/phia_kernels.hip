@@ -54,6 +54,7 @@ namespace phia {
 __global__ void __launch_bounds__(256) k_init(SweepArgs a)
 {
     const int64_t total = static_cast<int64_t>(a.R) * a.Np;
+    if (a.incstat && blockIdx.x == 0 && threadIdx.x < 4) a.incstat[threadIdx.x] = 0;
     for (int64_t idx = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; idx < total;
          idx += static_cast<int64_t>(gridDim.x) * blockDim.x) {
         const int64_t r = idx / a.Np;
@@ -2097,7 +2098,10 @@ int max_coresident_mfma(int path, int mt, int cbw, int jlds, int trace, int mh, 
 }
 
 // ---------------------------------------------------------------- argmin --
-__global__ void __launch_bounds__(256) k_argmin(const int64_t* bestE, int32_t R, int64_t* out)
+// out[0..2] = (energy, replica, *err or 0); with spins, the winner's n spins
+// follow at byte 64, so that one copy reads the whole result back.
+__global__ void __launch_bounds__(256) k_argmin(const int64_t* bestE, int32_t R, int64_t* out, const int8_t* bestS,
+                                                int32_t Np, int32_t n, const int32_t* err)
 {
     __shared__ int64_t sE[256];
     __shared__ int64_t sR[256];
@@ -2127,12 +2131,19 @@ __global__ void __launch_bounds__(256) k_argmin(const int64_t* bestE, int32_t R,
     if (threadIdx.x == 0) {
         out[0] = sE[0];
         out[1] = sR[0];
+        out[2] = err ? *err : 0;
+    }
+    if (bestS) {
+        const int8_t* src = bestS + (sR[0] < 0 ? 0 : sR[0]) * Np;
+        int8_t* dst = reinterpret_cast<int8_t*>(out) + 64;
+        for (int i = threadIdx.x; i < n; i += 256) dst[i] = src[i];
     }
 }
 
-hipError_t launch_argmin(const int64_t* bestE, int32_t R, int64_t* out2, hipStream_t st)
+hipError_t launch_argmin(const int64_t* bestE, int32_t R, int64_t* out, hipStream_t st, const int8_t* bestS, int32_t Np,
+                         int32_t n, const int32_t* err)
 {
-    hipLaunchKernelGGL(k_argmin, dim3(1), dim3(256), 0, st, bestE, R, out2);
+    hipLaunchKernelGGL(k_argmin, dim3(1), dim3(256), 0, st, bestE, R, out, bestS, Np, n, err);
     return hipGetLastError();
 }
 

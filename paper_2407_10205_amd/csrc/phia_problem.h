@@ -78,7 +78,7 @@ struct phia_problem {
     double* dJ64 = nullptr;
     double* dh64 = nullptr;
     int32_t* derr = nullptr;
-    int64_t* dscratch = nullptr;
+    int64_t* dscratch = nullptr;  // 64 bytes of results, then Np spins
     size_t base_bytes = 0;
     // packed couplings and fields on the host (dropped once resident unless
     // the upload is deferred), FP64 copies only for rounded input
@@ -114,13 +114,14 @@ struct phia_problem {
     float* dctab = nullptr;
     float* dx = nullptr;
     float* dv = nullptr;
-    int64_t* dbestE = nullptr;
+    int64_t* dbestE = nullptr;     // one allocation: energies [R], steps [R], spins [R][Np]
     int8_t* dbestS = nullptr;
     int64_t* dbestStep = nullptr;
     int64_t* detrace = nullptr;
     uint64_t* dxbits = nullptr;
     uint64_t* dpbuf = nullptr;
     uint32_t seq = 0;
+    bool err_live = false;  // launches since the last phia_sync may have raised the error word
     bool give_up = false;  // test hook: the device error word is raised before every sweep launch
     int32_t best_r = -1;
     size_t state_bytes = 0;

@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -609,8 +610,8 @@ void free_state(phia_problem* p)
     dfree(p->dx);
     dfree(p->dv);
     dfree(p->dbestE);
-    dfree(p->dbestS);
-    dfree(p->dbestStep);
+    p->dbestS = nullptr;
+    p->dbestStep = nullptr;
     dfree(p->dctab);
     dfree(p->detrace);
     dfree(p->dxbits);
@@ -922,7 +923,7 @@ phia_status phia_create(const double* J, const double* h, int32_t N, const phia_
     p->defer = o.defer_upload != 0;
     size_t* cnt = &p->base_bytes;
     if ((e = dalloc(reinterpret_cast<void**>(&p->derr), sizeof(int32_t) * 4, cnt)) != hipSuccess ||
-        (e = dalloc(reinterpret_cast<void**>(&p->dscratch), 64, cnt)) != hipSuccess ||
+        (e = dalloc(reinterpret_cast<void**>(&p->dscratch), 64 + static_cast<size_t>(Np), cnt)) != hipSuccess ||
         (e = dalloc(reinterpret_cast<void**>(&p->dincstat), 4 * sizeof(int64_t), cnt)) != hipSuccess) {
         phia_destroy(p);
         return fail(PHIA_ENOMEM, "device allocation failed: %s", hipGetErrorString(e));
@@ -1050,14 +1051,16 @@ phia_status setup_state(phia_problem* p, int32_t replicas, int64_t steps, const 
 {
     hipError_t e = hipSetDevice(p->dev);
     if (e != hipSuccess) return hip_fail(p, e, "hipSetDevice");
-    if (sync_first) {
-        e = p->st ? hipStreamSynchronize(p->st) : hipDeviceSynchronize();
-        if (e != hipSuccess) return hip_fail(p, e, "synchronise before re-allocation");
-    }
     const int mh = s->metropolis ? 1 : 0;
     const int ikick = s->initial_kick ? 1 : 0;
     reuse = p->dx && p->R == replicas && p->T == steps && p->trace == (p->detrace != nullptr) && p->mh == mh &&
             p->ikick == ikick && p->inc_mode_geo == p->inc_mode;
+    // before buffers are freed, or rewritten by a copy that is not ordered on
+    // the stream (the accept/reject step's table)
+    if (sync_first && (!reuse || mh)) {
+        e = p->st ? hipStreamSynchronize(p->st) : hipDeviceSynchronize();
+        if (e != hipSuccess) return hip_fail(p, e, "synchronise before re-allocation");
+    }
     if (!reuse) free_state(p);
     p->inc_mode_geo = p->inc_mode;
     p->R = replicas;
@@ -1078,12 +1081,15 @@ phia_status setup_state(phia_problem* p, int32_t replicas, int64_t steps, const 
     size_t* cnt = &p->state_bytes;
     if (!reuse && ((e = dalloc(reinterpret_cast<void**>(&p->dx), RN * sizeof(float), cnt)) != hipSuccess ||
                    (e = dalloc(reinterpret_cast<void**>(&p->dv), RN * sizeof(float), cnt)) != hipSuccess ||
-                   (e = dalloc(reinterpret_cast<void**>(&p->dbestS), RN, cnt)) != hipSuccess ||
-                   (e = dalloc(reinterpret_cast<void**>(&p->dbestE), sizeof(int64_t) * replicas, cnt)) != hipSuccess ||
-                   (e = dalloc(reinterpret_cast<void**>(&p->dbestStep), sizeof(int64_t) * replicas, cnt)) != hipSuccess ||
+                   (e = dalloc(reinterpret_cast<void**>(&p->dbestE), 2 * sizeof(int64_t) * replicas + RN, cnt)) !=
+                       hipSuccess ||
                    (e = dalloc(reinterpret_cast<void**>(&p->dctab), sizeof(float) * steps, cnt)) != hipSuccess)) {
         free_state(p);
         return fail(PHIA_ENOMEM, "state allocation failed: %s", hipGetErrorString(e));
+    }
+    if (!reuse) {
+        p->dbestStep = p->dbestE + replicas;
+        p->dbestS = reinterpret_cast<int8_t*>(p->dbestE + 2 * static_cast<size_t>(replicas));
     }
     if (p->trace && !reuse) {
         if ((e = dalloc(reinterpret_cast<void**>(&p->detrace), sizeof(int64_t) * replicas * steps, cnt)) !=
@@ -1139,8 +1145,6 @@ phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps, 
     // ctab is a pageable host vector; make the copy complete before it goes out of scope.
     hipError_t e = p->st ? hipStreamSynchronize(p->st) : hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(p, e, "schedule upload");
-    if ((e = hipMemsetAsync(p->dincstat, 0, 4 * sizeof(int64_t), p->st)) != hipSuccess)
-        return hip_fail(p, e, "counter reset");
     size_t* cnt = &p->state_bytes;
     if (reuse) {
         if ((st = setup_mh_geometry(p)) != PHIA_OK) return st;
@@ -1223,6 +1227,7 @@ phia_status phia_anneal_run(phia_problem* p, int64_t k_end)
     // workgroup had given up
     if (p->give_up && (e = hipMemsetAsync(p->derr, 0x02, 1, p->st)) != hipSuccess)
         return hip_fail(p, e, "error word");
+    if (p->give_up || p->geo.G > 1) p->err_live = true;
     if (p->geo.kind == 4) {
         e = launch_sweep_valu(valu_form(p), p->geo.rows, p->geo.j_lds != 0, a, p->st);
     } else if (p->geo.kind >= 1) {
@@ -1266,6 +1271,12 @@ phia_status phia_anneal_run(phia_problem* p, int64_t k_end)
     return PHIA_OK;
 }
 
+static phia_status timed_out(phia_problem* p, int32_t err)
+{
+    p->poisoned = true;
+    return fail(PHIA_EDEVICE, "a workgroup-group barrier timed out (device error word %d)", err);
+}
+
 phia_status phia_sync(phia_problem* p)
 {
     clear_error();
@@ -1274,13 +1285,13 @@ phia_status phia_sync(phia_problem* p)
     hipError_t e = hipSetDevice(p->dev);
     if (e == hipSuccess) e = p->st ? hipStreamSynchronize(p->st) : hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(p, e, "synchronise");
+    // only launches with an exchange between workgroups raise the error word
+    if (!p->err_live) return PHIA_OK;
     int32_t err = 0;
     e = hipMemcpy(&err, p->derr, sizeof err, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(p, e, "read device error word");
-    if (err) {
-        p->poisoned = true;
-        return fail(PHIA_EDEVICE, "a workgroup-group barrier timed out (device error word %d)", err);
-    }
+    if (err) return timed_out(p, err);
+    p->err_live = false;
     return PHIA_OK;
 }
 
@@ -1293,33 +1304,87 @@ phia_status phia_anneal(phia_problem* p, int32_t replicas, int64_t steps, const 
     return phia_sync(p);
 }
 
-static phia_status need_results(phia_problem* p)
+// Results exist; those of a batch are complete.
+static phia_status have_results(phia_problem* p)
 {
     phia_status st = check_usable(p);
     if (st != PHIA_OK) return st;
     if (!p->started || !p->has_run) return fail(PHIA_ESTATE, "no anneal steps have run");
-    if (p->batch) {
-        hipError_t e = batch_wait(p->batch);
-        if (e != hipSuccess) return hip_fail(p, e, "batch");
+    hipError_t e = hipSetDevice(p->dev);
+    if (e == hipSuccess && p->batch) e = batch_wait(p->batch);
+    if (e != hipSuccess) return hip_fail(p, e, p->batch ? "batch" : "hipSetDevice");
+    return PHIA_OK;
+}
+
+static phia_status need_results(phia_problem* p)
+{
+    phia_status st = have_results(p);
+    return st != PHIA_OK ? st : phia_sync(p);
+}
+
+// `rows` rows of w bytes from device memory of row pitch `pitch` into dense
+// host memory, after the work on the problem's stream.  Blocks of rows move
+// whole and are packed on the host: a strided copy to pageable memory takes
+// 6.5 us per row (512 rows of 2000 bytes: 3.3 ms, this way 0.1 ms).
+constexpr size_t kReadBlock = size_t(32) << 20;
+
+static hipError_t read_rows(phia_problem* p, void* dst, const void* src, size_t w, size_t pitch, size_t rows)
+{
+    const size_t per = w == pitch ? rows : std::min(rows, std::max<size_t>(1, kReadBlock / pitch));
+    std::unique_ptr<unsigned char[]> tmp;
+    if (w != pitch) {
+        tmp.reset(new (std::nothrow) unsigned char[pitch * per]);
+        if (!tmp) return hipErrorOutOfMemory;
     }
-    return phia_sync(p);
+    hipError_t e = hipSuccess;
+    for (size_t r0 = 0; r0 < rows && e == hipSuccess; r0 += per) {
+        const size_t n = std::min(per, rows - r0);
+        unsigned char* out = static_cast<unsigned char*>(dst) + r0 * w;
+        unsigned char* buf = tmp ? tmp.get() : out;
+        e = hipMemcpyAsync(buf, static_cast<const unsigned char*>(src) + r0 * pitch, pitch * n, hipMemcpyDeviceToHost,
+                           p->st);
+        if (e == hipSuccess) e = p->st ? hipStreamSynchronize(p->st) : hipDeviceSynchronize();
+        if (e == hipSuccess && tmp)
+            for (size_t r = 0; r < n; ++r) std::memcpy(out + r * w, buf + r * pitch, w);
+    }
+    return e;
+}
+
+// The best record: (energy units, replica) and, with spins, its N spins.  One
+// kernel gathers them with the error word and one copy brings them back.
+static phia_status read_best(phia_problem* p, int64_t* res, int8_t* spins)
+{
+    phia_status st = have_results(p);
+    if (st != PHIA_OK) return st;
+    const int n = spins ? p->N : 0;
+    alignas(8) unsigned char buf[64 + 16384];  // N <= 16384
+    hipError_t e = launch_argmin(p->dbestE, p->R, p->dscratch, p->st, spins ? p->dbestS : nullptr, p->Np, n,
+                                 p->err_live ? p->derr : nullptr);
+    if (e != hipSuccess) return hip_fail(p, e, "argmin launch");
+    if ((e = hipMemcpyAsync(buf, p->dscratch, n ? 64 + static_cast<size_t>(n) : 24, hipMemcpyDeviceToHost, p->st)) !=
+            hipSuccess ||
+        (e = p->st ? hipStreamSynchronize(p->st) : hipDeviceSynchronize()) != hipSuccess)
+        return hip_fail(p, e, "argmin readback");
+    int64_t r3[3];
+    std::memcpy(r3, buf, sizeof r3);
+    if (r3[2]) return timed_out(p, static_cast<int32_t>(r3[2]));
+    p->err_live = false;
+    res[0] = r3[0];
+    res[1] = r3[1];
+    if (spins) std::memcpy(spins, buf + 64, static_cast<size_t>(n));
+    p->best_r = static_cast<int32_t>(r3[1]);
+    return PHIA_OK;
 }
 
 phia_status phia_best_exact(phia_problem* p, int64_t* energy_units, int32_t* frac_bits, int32_t* replica)
 {
     clear_error();
-    phia_status st = need_results(p);
-    if (st != PHIA_OK) return st;
-    hipError_t e = launch_argmin(p->dbestE, p->R, p->dscratch, p->st);
-    if (e != hipSuccess) return hip_fail(p, e, "argmin launch");
     int64_t res[2];
-    if ((e = hipMemcpyAsync(res, p->dscratch, sizeof res, hipMemcpyDeviceToHost, p->st)) != hipSuccess ||
-        (e = p->st ? hipStreamSynchronize(p->st) : hipDeviceSynchronize()) != hipSuccess)
-        return hip_fail(p, e, "argmin readback");
+    phia_status st = read_best(p, res, nullptr);
+    if (st != PHIA_OK) return st;
     if (energy_units) *energy_units = res[0];
     if (frac_bits) *frac_bits = p->f;
     if (replica) *replica = static_cast<int32_t>(res[1]);
-    p->best_r = static_cast<int32_t>(res[1]);
     return PHIA_OK;
 }
 
@@ -1349,22 +1414,16 @@ phia_status phia_best_f64(phia_problem* p, double* energy)
 phia_status phia_best(phia_problem* p, double* energy, int8_t* spins)
 {
     clear_error();
-    int64_t E;
-    int32_t f, r;
-    phia_status st = phia_best_exact(p, &E, &f, &r);
+    int64_t res[2];
+    phia_status st = read_best(p, res, spins);
     if (st != PHIA_OK) return st;
     if (energy) {
         if (p->exact) {
-            *energy = std::ldexp(static_cast<double>(E), -f);
+            *energy = std::ldexp(static_cast<double>(res[0]), -p->f);
         } else {
             st = phia_best_f64(p, energy);
             if (st != PHIA_OK) return st;
         }
-    }
-    if (spins) {
-        hipError_t e = hipMemcpy(spins, p->dbestS + static_cast<size_t>(r) * p->Np, static_cast<size_t>(p->N),
-                                 hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return hip_fail(p, e, "best spins readback");
     }
     return PHIA_OK;
 }
@@ -1374,17 +1433,26 @@ phia_status phia_replica_best(phia_problem* p, int64_t* E, int8_t* S, int64_t* s
     clear_error();
     phia_status st = need_results(p);
     if (st != PHIA_OK) return st;
-    hipError_t e;
-    if (E && (e = hipMemcpy(E, p->dbestE, sizeof(int64_t) * p->R, hipMemcpyDeviceToHost)) != hipSuccess)
-        return hip_fail(p, e, "records readback");
-    if (step && (e = hipMemcpy(step, p->dbestStep, sizeof(int64_t) * p->R, hipMemcpyDeviceToHost)) != hipSuccess)
-        return hip_fail(p, e, "records readback");
-    if (S) {
-        if ((e = hipMemcpy2D(S, static_cast<size_t>(p->N), p->dbestS, static_cast<size_t>(p->Np),
-                             static_cast<size_t>(p->N), static_cast<size_t>(p->R), hipMemcpyDeviceToHost)) !=
-            hipSuccess)
-            return hip_fail(p, e, "records readback");
+    // energies, steps and spins are one allocation: one copy brings back what is read
+    const size_t R = static_cast<size_t>(p->R), eb = sizeof(int64_t) * R;
+    const bool spins_too = S && R * p->Np <= kReadBlock;
+    const size_t bytes = spins_too ? 2 * eb + R * p->Np : step ? 2 * eb : E ? eb : 0;
+    hipError_t e = hipSuccess;
+    if (bytes) {
+        std::unique_ptr<unsigned char[]> buf(new (std::nothrow) unsigned char[bytes]);
+        if (!buf) return fail(PHIA_ENOMEM, "host allocation failed");
+        e = hipMemcpyAsync(buf.get(), p->dbestE, bytes, hipMemcpyDeviceToHost, p->st);
+        if (e == hipSuccess) e = p->st ? hipStreamSynchronize(p->st) : hipDeviceSynchronize();
+        if (e != hipSuccess) return hip_fail(p, e, "records readback");
+        if (E) std::memcpy(E, buf.get(), eb);
+        if (step) std::memcpy(step, buf.get() + eb, eb);
+        if (spins_too)
+            for (size_t r = 0; r < R; ++r)
+                std::memcpy(S + r * p->N, buf.get() + 2 * eb + r * p->Np, static_cast<size_t>(p->N));
     }
+    if (S && !spins_too &&
+        (e = read_rows(p, S, p->dbestS, static_cast<size_t>(p->N), static_cast<size_t>(p->Np), R)) != hipSuccess)
+        return hip_fail(p, e, "records readback");
     return PHIA_OK;
 }
 
@@ -1435,9 +1503,9 @@ phia_status phia_get_state(phia_problem* p, float* x, float* v, int64_t* k)
     if (st != PHIA_OK) return st;
     const size_t pitch = sizeof(float) * p->Np, w = sizeof(float) * p->N;
     hipError_t e;
-    if (x && (e = hipMemcpy2D(x, w, p->dx, pitch, w, static_cast<size_t>(p->R), hipMemcpyDeviceToHost)) != hipSuccess)
+    if (x && (e = read_rows(p, x, p->dx, w, pitch, static_cast<size_t>(p->R))) != hipSuccess)
         return hip_fail(p, e, "state readback");
-    if (v && (e = hipMemcpy2D(v, w, p->dv, pitch, w, static_cast<size_t>(p->R), hipMemcpyDeviceToHost)) != hipSuccess)
+    if (v && (e = read_rows(p, v, p->dv, w, pitch, static_cast<size_t>(p->R))) != hipSuccess)
         return hip_fail(p, e, "state readback");
     if (k) *k = p->k;
     return PHIA_OK;
