@@ -54,9 +54,8 @@ typedef enum {
                                for sparse rows with 512 < Np <= 4096 (at most Np/64
                                nonzeros in every row)                                */
     PHIA_PATH_FP32 = 1,     /* FP32 couplings, VALU dot products (plain sweep)       */
-    PHIA_PATH_I8 = 2,       /* int8 couplings, int8 MFMA with int32 accumulation;
-                               with few replicas the VALU int8 dot-product sweep
-                               (see phia_anneal_start)                              */
+    PHIA_PATH_I8 = 2,       /* int8 couplings, int8 MFMA with int32 accumulation
+                               (FP4 operands where every coupling is one)           */
     PHIA_PATH_BF16HILO = 3, /* J = 256 hi + lo, two BF16 MFMA planes, FP32 accumulate */
     PHIA_PATH_ELL = 4       /* sparse rows: D (index, coupling) slots per row, spin
                                gathers on the VALUs; |J| <= 32767 units, N <= 4096 */
@@ -133,7 +132,11 @@ typedef struct {
                                exchange of one overlaps the other's compute; 3: the
                                persistent batch sweep (phia_batch_*); 4: the VALU
                                sweep, all columns of rows_per_block replicas per
-                               workgroup (FP32 and ELL paths, I8 with few replicas) */
+                               workgroup (FP32 and ELL paths, I8 with the initial
+                               kick); 5: the resident sweep, four replicas and all
+                               columns per workgroup, the couplings held in one
+                               CU's registers and LDS (I8, N <= 512, or N <= 832
+                               with FP4 operands)                               */
     int64_t steps;          /* T of the current anneal                               */
     int64_t step;           /* next step to run                                      */
     int64_t max_abs_J;      /* max |J| in units                                      */
@@ -190,18 +193,18 @@ phia_status phia_anneal_noalloc(phia_problem* p, int32_t replicas, int64_t steps
                                 int64_t* best_energy_units, int32_t* best_replica);
 
 /* Largest replica count for which an anneal on the I8 path takes the VALU
- * int8 dot-product sweep by default, for padded size Np (0: never).  Below it
- * J.s is a matrix-vector product per replica and the sweep is bound by the
- * stream of J, which 16-row matrix-core tiles would mostly pad; the value is
- * the crossover measured against the matrix-core sweeps on MI355X. */
+ * int8 dot-product sweep by default, for padded size Np (0: never).  It is 0
+ * at every size now that the resident sweep runs J.s of few replicas on the
+ * matrix cores in less time; the environment variable PHIA_VALU_CROSSOVER
+ * replaces it.  (A problem whose row sums are too large for the resident
+ * sweep's energy sums takes the VALU sweep with few replicas.) */
 int32_t phia_valu_crossover(int32_t Np);
 
 /* Allocate replica state and draw x ~ N(0, I) (App. A, A3) for step 0.
  * Enqueued on the problem's stream; returns without waiting.  The sweep's
  * launch geometry is fixed here from (path, Np, replicas): on the I8 path,
- * anneals of few replicas (replicas <= phia_valu_crossover(Np), no
- * accept/reject step) run the VALU int8 dot-product sweep, where J.s is a
- * matrix-vector product per replica; larger ones the matrix-core sweeps.
+ * couplings that one CU holds run the resident sweep (sweep_kernel 5), larger
+ * ones and the accept/reject step the column-split matrix-core sweeps.
  * A tuned or cached geometry (phia_autotune) takes precedence. */
 phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps,
                               const phia_schedule* schedule, uint64_t seed);

@@ -56,28 +56,9 @@ constexpr int kSquadMaxNp = 256;       // largest instance of a squad
 constexpr uint32_t kFixedLds = 512;
 
 __host__ __device__ inline int nkb4_of(int Np) { return (Np + 127) / 128; }
-// A pointer that every lane of the wave holds alike, as a scalar (the
-// arguments of a function that is not inlined arrive in VGPRs).
-template <class T>
-__device__ __forceinline__ T* uniform_ptr(T* p)
-{
-    const uint64_t u = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32));
-    return reinterpret_cast<T*>(static_cast<uint64_t>(hi) << 32 | lo);
-}
-
 // LDS passed to a function that is not inlined keeps its address space (a
 // generic pointer would turn every access into a flat one).
 typedef __attribute__((address_space(3))) unsigned char LdsByte;
-
-// The kick factors as scalar loads (a flat load would count as an LDS access
-// too, and the step's first LDS wait would wait for it).
-typedef const __attribute__((address_space(4))) float* ConstF;
-__device__ __forceinline__ ConstF scalar_table(const float* p)
-{
-    return (ConstF)(uint64_t)uniform_ptr(p);
-}
 
 // Column of element j (0 .. 3) of lane group lg within its 16-column block.
 // The FP4 codes of 8 columns are ordered 0 4 1 5 2 6 3 7 in LDS (the packed

@@ -51,6 +51,25 @@ __device__ __forceinline__ void gauss_block(uint64_t seed, uint64_t replica, uin
     for (int p = 0; p < 4; ++p) gauss_pair(o.w[p], g[2 * p], g[2 * p + 1]);
 }
 
+// A pointer that every lane of the wave holds alike, as a scalar (the
+// arguments of a function that is not inlined arrive in VGPRs).
+template <class T>
+__device__ __forceinline__ T* uniform_ptr(T* p)
+{
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32));
+    return reinterpret_cast<T*>(static_cast<uint64_t>(hi) << 32 | lo);
+}
+
+// The kick factors as scalar loads (a flat load would count as an LDS access
+// too, and the step's first LDS wait would wait for it).
+typedef const __attribute__((address_space(4))) float* ConstF;
+__device__ __forceinline__ ConstF scalar_table(const float* p)
+{
+    return (ConstF)(uint64_t)uniform_ptr(p);
+}
+
 // Value v of lane `src` (all lanes of the wave active).
 __device__ __forceinline__ float lane_read(int src, float v)
 {

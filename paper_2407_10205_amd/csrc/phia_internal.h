@@ -92,6 +92,11 @@ __host__ __device__ inline size_t valu_jl_offset(int rb, int Np) { return (stati
 size_t valu_lds_bytes(int form, int rb, int Np, bool jl);
 bool valu_variant(int form, int rb, int mh, bool jl);  // a compiled (form, rows, accept/reject, J in LDS) combination
 hipError_t launch_sweep_valu(int form, int rb, bool jl, const SweepArgs& a, hipStream_t st);
+// Resident sweep (k_sweep_res): four replicas and all columns per workgroup, the
+// couplings (int8, or FP4 operands) in VGPRs and LDS.  0 bytes: N does not fit.
+constexpr int kResReplicas = 4;
+size_t sweep_res_lds_bytes(int N, int fp4);
+hipError_t launch_sweep_res(int fp4, const SweepArgs& a, hipStream_t st);
 hipError_t launch_sweep_mfma(int path, int mt, int cbw, const SweepArgs& a, size_t lds_bytes, hipStream_t st);
 size_t sweep_mfma_lds_bytes(int path, int mt, const SweepArgs& a);
 // out: (energy, replica, *err or 0), then with bestS the winner's n spins at byte 64

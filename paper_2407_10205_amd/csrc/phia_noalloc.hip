@@ -133,7 +133,7 @@ extern "C" phia_status phia_anneal_noalloc(phia_problem* p, int32_t replicas, in
         return hip_fail(p, e, "scratch set-up");
 
     SweepArgs a = sweep_args(p);
-    a.J = g.kind == 2 ? p->dJ4 : p->dJ;
+    a.J = g.kind == 2 || (g.kind == 5 && g.fp4) ? p->dJ4 : p->dJ;
     a.ctab = dctab;
     a.eps = s->eps;
     a.gamma = s->gamma;
@@ -175,7 +175,9 @@ extern "C" phia_status phia_anneal_noalloc(phia_problem* p, int32_t replicas, in
     a.k1 = steps;
 
     if ((e = launch_init(a, stream)) != hipSuccess) return hip_fail(p, e, "init kernel launch");
-    if (g.kind == 4) {
+    if (g.kind == 5) {
+        e = launch_sweep_res(g.fp4, a, stream);
+    } else if (g.kind == 4) {
         e = launch_sweep_valu(p->path == PHIA_PATH_FP32 ? kValuFp32 : p->path == PHIA_PATH_ELL ? kValuEll : kValuDot8,
                               g.rows, g.j_lds != 0, a, stream);
     } else if (g.kind >= 1) {

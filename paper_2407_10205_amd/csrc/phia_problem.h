@@ -13,7 +13,9 @@ namespace phia {
 struct Geometry {
     bool ok = false;
     int kind = 0;      // 0: k_sweep_mfma; k_sweep_pp (interleaved sub-blocks) with 1: int8, 2: FP4 operands;
-                       // 3: persistent batch sweep (k_batch_fp4); 4: VALU sweep (k_sweep_valu)
+                       // 3: persistent batch sweep (k_batch_fp4); 4: VALU sweep (k_sweep_valu);
+                       // 5: resident sweep (k_sweep_res)
+    int fp4 = 0;       // kind 5: FP4 operands (else int8)
     int mt = 1;        // 16-replica row tiles per workgroup
     int cbw = 2;       // max 16-column blocks per wave
     int G = 1;         // workgroups splitting the columns of one replica block

@@ -246,6 +246,7 @@ static const char* path_name(int path)
 static bool make_geometry(phia_problem* p, int R, int mt, int cbw, int G, int j_lds, Geometry& g, int xcd = -1);
 static bool make_geometry_pp(phia_problem* p, int R, int G, int fp4, Geometry& g, int xcd = -1, int jg = 0);
 static bool make_geometry_valu(phia_problem* p, int R, int rb, Geometry& g);
+static bool make_geometry_res(phia_problem* p, int R, Geometry& g);
 
 static bool lookup_tune_cache(phia_problem* p, int R)
 {
@@ -261,7 +262,8 @@ static bool lookup_tune_cache(phia_problem* p, int R)
     while (std::fscanf(f, "%31s %d %d %d %d %d %d %d %d %d %lf", tag, &pa, &np, &r, &kind, &mt, &cbw, &G, &jl, &xcd,
                        &us) == 11) {
         if (std::strcmp(tag, "phia-tune4") == 0 && pa == p->path && np == p->Np && r == R &&
-            (kind == 4   ? make_geometry_valu(p, R, mt, g)
+            (kind == 5   ? make_geometry_res(p, R, g)
+             : kind == 4 ? make_geometry_valu(p, R, mt, g)
              : kind >= 1 ? make_geometry_pp(p, R, G, kind == 2, g, xcd, kind == 1 && jl == 0)
                          : make_geometry(p, R, mt, cbw, G, jl, g, xcd))) {
             p->geo = g;
@@ -400,24 +402,58 @@ static bool make_geometry_pp(phia_problem* p, int R, int G, int fp4, Geometry& g
     return true;
 }
 
+// Resident sweep (k_sweep_res): int8 path, four replicas and all columns per
+// workgroup, couplings in VGPRs and LDS as FP4 operands where the problem has
+// them (and its row sums stay exact in FP32), else int8.  False if it does
+// not apply.
+static bool make_geometry_res(phia_problem* p, int R, Geometry& g)
+{
+    if (p->path != PHIA_PATH_I8 || p->one_block_kernel || p->mh || p->ikick) return false;
+    const int64_t row = 2 * p->maxrow * p->N;  // bounds |sum_i s_i (I_i + h_i)|
+    const int fp4 = p->has_j4 && row < (int64_t(1) << 24) && sweep_res_lds_bytes(p->N, 1) > 0;
+    if (!fp4 && (row >= (int64_t(1) << 31) || sweep_res_lds_bytes(p->N, 0) == 0)) return false;
+    g = Geometry{};
+    g.ok = true;
+    g.kind = 5;
+    g.fp4 = fp4;
+    g.mt = 1;
+    g.cbw = 1;
+    g.G = 1;
+    g.j_lds = 1;
+    g.rows = kResReplicas;
+    g.nblocks = (R + g.rows - 1) / g.rows;
+    g.ngroups = g.nblocks;
+    g.lds = sweep_res_lds_bytes(p->N, fp4);
+    return true;
+}
+
 // Replica counts that take the VALU sweeps by default.
 constexpr int kValuTuneMaxR = 64;  // the autotuner also times the int8 VALU sweep up to here
 
-// Largest replica count for which an int8 anneal takes the VALU dot-product
-// sweep (measured crossover against the matrix-core sweeps on MI355X).
+// Largest replica count for which an int8 anneal that the resident sweep does
+// not hold takes the VALU dot-product sweep (measured crossover against the
+// other matrix-core sweeps on MI355X).
 // While J fits in LDS (Np <= 384) one workgroup per replica finishes a step
 // sooner than the matrix-core sweeps (0.94 against 1.21 us at Np = 64, 1.3
 // against 2.6 us at Np = 256, 2.05 against 2.77 us at Np = 384) until the
 // replicas outnumber the workgroups the CUs hold at once (J of 64 KiB: two
 // per CU, above 80 KiB: one); beyond Np = 384 the column-split matrix-core
-// sweeps win at every replica count.  PHIA_VALU_CROSSOVER=n replaces the
-// rule (tuning experiments; 0: never).
-int valu_crossover(int Np)
+// sweeps win at every replica count.
+static int valu_fallback(int Np)
 {
-    if (const char* env = std::getenv("PHIA_VALU_CROSSOVER")) return std::atoi(env);
     if (Np <= 64) return 1024;
     if (Np <= 256) return 512;
     if (Np <= 384) return 256;
+    return 0;
+}
+
+// The VALU sweep is not the default where the resident sweep holds the
+// couplings: four replicas per workgroup on the matrix cores take 0.40 us per
+// step at Np = 64 and 0.70 us at Np = 256, at 4 to 1024 replicas.
+// PHIA_VALU_CROSSOVER=n replaces the rule (tuning experiments).
+int valu_crossover(int)
+{
+    if (const char* env = std::getenv("PHIA_VALU_CROSSOVER")) return std::atoi(env);
     return 0;
 }
 
@@ -480,6 +516,10 @@ static std::vector<Geometry> candidate_geometries(phia_problem* p, int R)
         }
         return out;
     }
+    {
+        Geometry g;
+        if (make_geometry_res(p, R, g)) out.push_back(g);
+    }
     if (p->path == PHIA_PATH_I8 && R <= kValuTuneMaxR)
         for (int rb : {1, 2}) {
             Geometry g;
@@ -519,8 +559,30 @@ static std::vector<Geometry> candidate_geometries(phia_problem* p, int R)
 // Default geometry without tuning: fewest passes over the replica blocks,
 // then the fewest owned elements per workgroup, then J in LDS.
 // PHIA_GEOMETRY="mt,G,jlds[,cbw[,xcd]]" or "pp,G[,xcd]" / "pp4,G[,xcd]" /
-// "ppg,G[,xcd]" (interleaved, int8 J streamed from global memory) forces
-// one candidate (tuning experiments).
+// "ppg,G[,xcd]" (interleaved, int8 J streamed from global memory), "valu,rb"
+// or "res" forces one candidate (tuning experiments).
+// Replica counts at which the resident sweep is the default where it fits,
+// in us per step, it / the best of the other sweeps:
+//   N = 16    0.40 / 0.95 at 64 replicas, 0.63 / 3.1 at 16384;
+//   N = 96    0.65 / 1.42 at 2048, 1.3 / 1.44 at 4096, 4.7 / 4.1 at 16384;
+//   N = 192   1.3 / 2.3 at 2048, 2.5 / 2.4 at 4096, 9.6 / 6.5 at 16384;
+//   N = 256   0.77 / 2.7 at 1024, 1.5 / 2.7 at 2048, 2.9 / 2.9 at 4096;
+//   N = 320   1.7 / 2.4 at 2048, 12.9 / 26 at 16384;
+//   N = 437   1.23 / 3.0 (int8) at 1024, 17 / 33 at 16384;
+//   N = 800   1.70 / 2.56 at 64, 2.0 / 2.9 at 1024, 28 / 79 at 16384.
+// Its workgroups of four replicas run one or two to a CU, so its time grows
+// with every further 1024 or 2048 replicas; up to 256 columns the one-block
+// kernel of 16 or 32 replicas per workgroup fills the chip only at 4096 or
+// 8192 and then overtakes it.
+// A traced anneal of 1024 replicas or more keeps the column split beyond 512
+// columns: a diagnostic run, by which the parity tests reach those kernels.
+static bool resident_wins(const phia_problem* p, int R)
+{
+    if (p->trace && p->Np > 512 && R >= 1024) return false;
+    if (p->Np <= 64 || p->Np > 256) return true;
+    return R <= (p->Np <= 128 ? 4096 : 3072);
+}
+
 static void choose_geometry(phia_problem* p, int R)
 {
     p->geo.ok = false;
@@ -535,6 +597,11 @@ static void choose_geometry(phia_problem* p, int R)
     int f_mt = 0, f_G = 0, f_j = -1, f_c = kCbwMax;
     if (const char* env = std::getenv("PHIA_GEOMETRY")) {
         int f_x = -1;
+        if (std::strcmp(env, "res") == 0) {
+            Geometry g;
+            if (make_geometry_res(p, R, g)) p->geo = g;
+            return;
+        }
         if (std::sscanf(env, "valu,%d", &f_G) == 1) {
             Geometry g;
             if (make_geometry_valu(p, R, f_G, g)) p->geo = g;
@@ -572,8 +639,12 @@ static void choose_geometry(phia_problem* p, int R)
         make_geometry_valu(p, R, p->path == PHIA_PATH_FP32 ? kFp32Rows : ell_rows(R), p->geo);
         return;
     }
-    // Few replicas on the int8 path: the VALU dot-product sweep.
     if (p->path == PHIA_PATH_I8 && R <= valu_crossover(p->Np) && make_geometry_valu(p, R, valu_rows(R), p->geo))
+        return;
+    // Couplings that one CU holds: the resident sweep (resident_wins).
+    if (resident_wins(p, R) && make_geometry_res(p, R, p->geo)) return;
+    // Few replicas on the int8 path: the VALU dot-product sweep.
+    if (p->path == PHIA_PATH_I8 && R <= valu_fallback(p->Np) && make_geometry_valu(p, R, valu_rows(R), p->geo))
         return;
     // Fewest passes over the replica blocks first; among those a geometry
     // without column split, else the interleaved kernel with the smallest
@@ -583,11 +654,11 @@ static void choose_geometry(phia_problem* p, int R)
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->dev) != hipSuccess || cus < 1) cus = 256;
     int min_iters = 1 << 30;
     for (const Geometry& g : cands)
-        if (g.kind != 4) min_iters = std::min(min_iters, (g.nblocks + g.ngroups - 1) / g.ngroups);
+        if (g.kind != 4 && g.kind != 5) min_iters = std::min(min_iters, (g.nblocks + g.ngroups - 1) / g.ngroups);
     double best = 0;
     for (const Geometry& g : cands) {
         const int iters = (g.nblocks + g.ngroups - 1) / g.ngroups;
-        if (iters != min_iters || g.kind == 4) continue;  // the VALU sweep: by the crossover rule or tuning only
+        if (iters != min_iters || g.kind == 4 || g.kind == 5) continue;  // those: by the rules above or tuning only
         const int cbs_max = (p->Np / 16 + g.G - 1) / g.G;
         const double elems = static_cast<double>(g.rows) * cbs_max * 16;
         double cost = g.kind >= 1 ? 1e6 + 2 * g.G - (g.kind == 2 ? 1 : 0) + (g.j_lds ? 0 : 0.5)
@@ -706,7 +777,7 @@ SweepArgs sweep_args(const phia_problem* p)
     a.N = p->N;
     a.Np = p->Np;
     a.h = p->dh;
-    a.J = p->geo.kind == 2 ? p->dJ4 : p->dJ;
+    a.J = p->geo.kind == 2 || (p->geo.kind == 5 && p->geo.fp4) ? p->dJ4 : p->dJ;
     a.ell_d = p->ell_d;
     a.ikick = p->ikick;
     a.ctab = p->dctab;
@@ -1228,7 +1299,9 @@ phia_status phia_anneal_run(phia_problem* p, int64_t k_end)
     if (p->give_up && (e = hipMemsetAsync(p->derr, 0x02, 1, p->st)) != hipSuccess)
         return hip_fail(p, e, "error word");
     if (p->give_up || p->geo.G > 1) p->err_live = true;
-    if (p->geo.kind == 4) {
+    if (p->geo.kind == 5) {
+        e = launch_sweep_res(p->geo.fp4, a, p->st);
+    } else if (p->geo.kind == 4) {
         e = launch_sweep_valu(valu_form(p), p->geo.rows, p->geo.j_lds != 0, a, p->st);
     } else if (p->geo.kind >= 1) {
         // 24-bit tags: launches of at most `chunk` steps, and the sequence
@@ -1559,7 +1632,8 @@ phia_status phia_autotune(phia_problem* p, int32_t replicas, int64_t probe_steps
     // Candidates that need more passes over the replica blocks than twice
     // the best one cannot win; skip them.
     int min_iters = 1 << 30;
-    for (const Geometry& g : cands) min_iters = std::min(min_iters, (g.nblocks + g.ngroups - 1) / g.ngroups);
+    for (const Geometry& g : cands)
+        if (g.kind != 5) min_iters = std::min(min_iters, (g.nblocks + g.ngroups - 1) / g.ngroups);
     hipError_t e = hipSetDevice(p->dev);
     if (e != hipSuccess) return hip_fail(p, e, "hipSetDevice");
     hipEvent_t e0 = nullptr, e1 = nullptr;
