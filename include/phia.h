@@ -53,7 +53,8 @@ typedef enum {
     PHIA_PATH_AUTO = 0,     /* I8 if |J| <= 127 units, else BF16HILO, else FP32; ELL
                                for sparse rows with 512 < Np <= 4096 (at most Np/64
                                nonzeros in every row)                                */
-    PHIA_PATH_FP32 = 1,     /* FP32 couplings, VALU dot products (plain sweep)       */
+    PHIA_PATH_FP32 = 1,     /* FP32 couplings: three int8 planes on the matrix cores,
+                               or VALU dot products (plain sweep)                    */
     PHIA_PATH_I8 = 2,       /* int8 couplings, int8 MFMA with int32 accumulation
                                (FP4 operands where every coupling is one)           */
     PHIA_PATH_BF16HILO = 3, /* J = 256 hi + lo, two BF16 MFMA planes, FP32 accumulate */
@@ -136,7 +137,10 @@ typedef struct {
                                kick); 5: the resident sweep, four replicas and all
                                columns per workgroup, the couplings held in one
                                CU's registers and LDS (I8, N <= 512, or N <= 832
-                               with FP4 operands)                               */
+                               with FP4 operands); 6: the split sweep, columns of
+                               4 or 16 replicas over a group of workgroups with
+                               the couplings in registers as int8 planes (FP32,
+                               BF16HILO, I8, Np <= 2048)                        */
     int64_t steps;          /* T of the current anneal                               */
     int64_t step;           /* next step to run                                      */
     int64_t max_abs_J;      /* max |J| in units                                      */
@@ -203,8 +207,9 @@ int32_t phia_valu_crossover(int32_t Np);
 /* Allocate replica state and draw x ~ N(0, I) (App. A, A3) for step 0.
  * Enqueued on the problem's stream; returns without waiting.  The sweep's
  * launch geometry is fixed here from (path, Np, replicas): on the I8 path,
- * couplings that one CU holds run the resident sweep (sweep_kernel 5), larger
- * ones and the accept/reject step the column-split matrix-core sweeps.
+ * couplings that one CU holds run the resident sweep (sweep_kernel 5); larger
+ * ones, FP32 and 16-bit couplings the split sweep (6); the accept/reject step,
+ * energy traces and Np > 2048 the other sweeps.
  * A tuned or cached geometry (phia_autotune) takes precedence. */
 phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps,
                               const phia_schedule* schedule, uint64_t seed);

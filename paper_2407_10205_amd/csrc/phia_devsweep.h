@@ -209,4 +209,53 @@ __device__ __forceinline__ long long wave_sum16_i64(long long v)
     return v;
 }
 
+// Unpack one 16-bit sign word (bit t set: spin +1) into 16 int8 or 16 bf16
+// spins of an S row.
+template <int ESZ>
+__device__ __forceinline__ void unpack_signs(uint32_t w, unsigned char* dst)
+{
+    if (ESZ == 1) {
+        uint32_t d[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint32_t n = (w >> (4 * t)) & 0xfu;
+            const uint32_t m = (n * 0x00204081u) & 0x01010101u;  // bit i -> byte i
+            d[t] = 0xffffffffu - 0xfeu * m;                      // 0x01 or 0xff per byte
+        }
+        *reinterpret_cast<uint4*>(dst) = uint4{d[0], d[1], d[2], d[3]};
+    } else {
+        uint32_t d[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const uint32_t n = (w >> (2 * t)) & 3u;
+            const uint32_t m = (n & 1u) | ((n & 2u) << 15);      // bit i -> half i
+            d[t] = 0xbf80bf80u - 0x8000u * m;                    // bf16 +1 / -1
+        }
+        uint4* q = reinterpret_cast<uint4*>(dst);
+        q[0] = uint4{d[0], d[1], d[2], d[3]};
+        q[1] = uint4{d[4], d[5], d[6], d[7]};
+    }
+}
+
+// Sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the lanes of one replica
+// in the transposed products), in each of them.  The gfx950 lane swaps
+// exchange rows 2i + 1 of the first operand with rows 2i of the second
+// (permlane16), then the upper half of the first with the lower half of the
+// second (permlane32); applied to two copies of v, the two outputs add up to
+// v[l] + v[partner] in every lane.  VALU only: no LDS round trip queued
+// behind the other waves' operand reads.  Written in assembly so that the
+// two copies stay two registers (the compiler may otherwise take one output
+// for the other); the nop covers the VALU-write-to-permlane-read hazard.
+// The whole wave must be active.
+__device__ __forceinline__ uint32_t replica_sum_u(uint32_t v)
+{
+    uint32_t a = v, b = v;
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    v = a + b;
+    a = v;
+    b = v;
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return a + b;
+}
+
 }  // namespace phia

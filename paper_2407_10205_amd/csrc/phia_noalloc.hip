@@ -92,28 +92,37 @@ extern "C" phia_status phia_anneal_noalloc(phia_problem* p, int32_t replicas, in
     unsigned char* base = nullptr;
     if ((e = scratch_address(p->dev, &base)) != hipSuccess) return hip_fail(nullptr, e, "scratch address");
 
-    const Geometry g = plain_geometry(p, replicas, s->initial_kick ? 1 : 0);
-    if (!g.ok) return fail(PHIA_ERANGE, "no kernel geometry fits N = %d on this device", p->N);
-    const bool group = g.kind != 4 && g.G > 1;
     const size_t ncb = static_cast<size_t>(p->Np / 16);
-    const size_t xb = group ? 2 * static_cast<size_t>(g.ngroups) * g.rows * ncb * sizeof(uint64_t) : 0;
-    const size_t pb = group ? 2 * static_cast<size_t>(g.ngroups) * g.G * g.rows * 2 * sizeof(uint64_t) : 0;
     // scratch layout: error word, argmin result, kick factors, exchange words, partial energies
     const size_t err_off = 0, arg_off = 256, ctab_off = 512;
     const size_t xb_off = ctab_off + round256(sizeof(float) * static_cast<size_t>(steps));
-    const size_t pb_off = xb_off + round256(xb);
-    const size_t need = pb_off + round256(pb);
+    Geometry g;
+    bool group = false;
+    size_t xb = 0, pb = 0, pb_off = 0, need = 0;
+    auto plan = [&](bool split) {
+        g = plain_geometry(p, replicas, s->initial_kick ? 1 : 0, split);
+        group = g.ok && g.G > 1;
+        xb = group ? 2 * static_cast<size_t>(g.ngroups) * g.rows * ncb * sizeof(uint64_t) : 0;
+        pb = group && g.kind != 6 ? 2 * static_cast<size_t>(g.ngroups) * g.G * g.rows * 2 * sizeof(uint64_t) : 0;
+        pb_off = xb_off + round256(xb);
+        need = pb_off + round256(pb);
+    };
+    plan(true);
+    // steps whose kick factors leave no room for the split sweep's words
+    if (g.ok && g.kind == 6 && need > kScratchBytes) plan(false);
+    if (!g.ok) return fail(PHIA_ERANGE, "no kernel geometry fits N = %d on this device", p->N);
     if (need > kScratchBytes)
         return fail(PHIA_ERANGE, "this anneal needs %zu bytes of scratch; phia_anneal_noalloc holds %zu", need,
                     kScratchBytes);
     const int64_t iters = (g.nblocks + g.ngroups - 1) / g.ngroups;
     constexpr int64_t kChunk = int64_t(1) << 22;  // steps per launch of the interleaved sweep
-    if (group) {
+    if (group && g.kind != 6) {
         // one call never restarts the exchange tags: 24 bits (interleaved
         // sweep) or 32 bits of sequence numbers must cover the whole anneal
         // (a launch of n steps takes n + 1 per pass over the replica blocks)
-        const int64_t room = g.kind >= 1 ? (int64_t(1) << 24) - 2 : (int64_t(1) << 32) - 2;
-        const int64_t launches = g.kind >= 1 ? (steps + kChunk - 1) / kChunk : 1;
+        const bool tag24 = g.kind == 1 || g.kind == 2;
+        const int64_t room = tag24 ? (int64_t(1) << 24) - 2 : (int64_t(1) << 32) - 2;
+        const int64_t launches = tag24 ? (steps + kChunk - 1) / kChunk : 1;
         if (iters * (steps + launches) > room)
             return fail(PHIA_ERANGE, "%lld steps x %lld block passes exceed the exchange tags of one call",
                         static_cast<long long>(steps), static_cast<long long>(iters));
@@ -129,7 +138,7 @@ extern "C" phia_status phia_anneal_noalloc(phia_problem* p, int32_t replicas, in
     if ((e = hipMemcpy(dctab, ctab.data(), sizeof(float) * ctab.size(), hipMemcpyHostToDevice)) != hipSuccess ||
         (e = zero_words(derr, 256, stream)) != hipSuccess ||
         (group && (e = zero_words(base + xb_off, xb, stream)) != hipSuccess) ||
-        (group && (e = zero_words(base + pb_off, pb, stream)) != hipSuccess))
+        (pb && (e = zero_words(base + pb_off, pb, stream)) != hipSuccess))
         return hip_fail(p, e, "scratch set-up");
 
     SweepArgs a = sweep_args(p);
@@ -160,7 +169,7 @@ extern "C" phia_status phia_anneal_noalloc(phia_problem* p, int32_t replicas, in
     a.inc = g.inc;
     a.incstat = nullptr;
     a.xbits = group ? reinterpret_cast<uint64_t*>(base + xb_off) : nullptr;
-    a.pbuf = group ? reinterpret_cast<uint64_t*>(base + pb_off) : nullptr;
+    a.pbuf = pb ? reinterpret_cast<uint64_t*>(base + pb_off) : nullptr;
     a.seq_base = 0;
     a.err = derr;
     a.mh = 0;
@@ -180,6 +189,8 @@ extern "C" phia_status phia_anneal_noalloc(phia_problem* p, int32_t replicas, in
     } else if (g.kind == 4) {
         e = launch_sweep_valu(p->path == PHIA_PATH_FP32 ? kValuFp32 : p->path == PHIA_PATH_ELL ? kValuEll : kValuDot8,
                               g.rows, g.j_lds != 0, a, stream);
+    } else if (g.kind == 6) {
+        e = launch_sweep_split(a, g.planes, stream);
     } else if (g.kind >= 1) {
         // launches of at most 2^22 steps, sequence numbers running on
         uint32_t seq = 0;

@@ -14,8 +14,9 @@ struct Geometry {
     bool ok = false;
     int kind = 0;      // 0: k_sweep_mfma; k_sweep_pp (interleaved sub-blocks) with 1: int8, 2: FP4 operands;
                        // 3: persistent batch sweep (k_batch_fp4); 4: VALU sweep (k_sweep_valu);
-                       // 5: resident sweep (k_sweep_res)
+                       // 5: resident sweep (k_sweep_res); 6: split sweep (k_sweep_split)
     int fp4 = 0;       // kind 5: FP4 operands (else int8)
+    int planes = 1;    // kind 6: int8 planes of the couplings
     int mt = 1;        // 16-replica row tiles per workgroup
     int cbw = 2;       // max 16-column blocks per wave
     int G = 1;         // workgroups splitting the columns of one replica block
@@ -50,7 +51,7 @@ void release_resident(::phia_problem* p);
 int valu_crossover(int Np);
 phia_status setup_mh_geometry(::phia_problem* p);
 SweepArgs sweep_args(const ::phia_problem* p);
-Geometry plain_geometry(::phia_problem* p, int R, int ikick = 0);
+Geometry plain_geometry(::phia_problem* p, int R, int ikick = 0, bool split = true);
 phia_status launch_batch_chunk(::phia_problem* const* probs, int count, const int64_t* k_end, hipStream_t st,
                                SweepArgs*& dtab, size_t& cap);
 phia_status launch_group_chunk(::phia_problem* const* probs, int count, const int64_t* k_end, hipStream_t st,
@@ -92,6 +93,7 @@ struct phia_problem {
     size_t jres_bytes = 0;  // device bytes of those copies when resident
     // anneal
     bool started = false, has_run = false, trace = false;
+    bool no_split = false;          // leave the split sweep out of choose_geometry
     bool one_block_kernel = false;  // restrict geometries to k_sweep_mfma (server table launches)
     int inc_mode = -1;              // flip-incremental update: -1 default, 0 off, 1 on where a variant exists
     int inc_mode_geo = -1;          // inc_mode when the current state and geometry were set up

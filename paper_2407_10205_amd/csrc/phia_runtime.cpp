@@ -229,7 +229,7 @@ static void pack_bf16(const std::vector<int32_t>& Ji, int N, int Np, std::vector
 // ------------------------------------------------------- kernel geometry --
 // ------------------------------------------------------- tuning cache --
 // One line per tuned shape: "phia-tune4 path Np R kind mt cbw G jlds xcd us_per_step"
-// (kind 4, the VALU sweep: replicas per workgroup in place of mt).
+// (kinds 4 and 6, the VALU and the split sweep: replicas per workgroup or group in place of mt).
 static const char* tune_cache_path() { return std::getenv("PHIA_TUNE_CACHE"); }
 
 static const char* path_name(int path)
@@ -247,6 +247,7 @@ static bool make_geometry(phia_problem* p, int R, int mt, int cbw, int G, int j_
 static bool make_geometry_pp(phia_problem* p, int R, int G, int fp4, Geometry& g, int xcd = -1, int jg = 0);
 static bool make_geometry_valu(phia_problem* p, int R, int rb, Geometry& g);
 static bool make_geometry_res(phia_problem* p, int R, Geometry& g);
+static bool make_geometry_split(phia_problem* p, int R, int rows, int G, Geometry& g);
 
 static bool lookup_tune_cache(phia_problem* p, int R)
 {
@@ -262,7 +263,8 @@ static bool lookup_tune_cache(phia_problem* p, int R)
     while (std::fscanf(f, "%31s %d %d %d %d %d %d %d %d %d %lf", tag, &pa, &np, &r, &kind, &mt, &cbw, &G, &jl, &xcd,
                        &us) == 11) {
         if (std::strcmp(tag, "phia-tune4") == 0 && pa == p->path && np == p->Np && r == R &&
-            (kind == 5   ? make_geometry_res(p, R, g)
+            (kind == 6   ? make_geometry_split(p, R, mt, G, g)
+             : kind == 5 ? make_geometry_res(p, R, g)
              : kind == 4 ? make_geometry_valu(p, R, mt, g)
              : kind >= 1 ? make_geometry_pp(p, R, G, kind == 2, g, xcd, kind == 1 && jl == 0)
                          : make_geometry(p, R, mt, cbw, G, jl, g, xcd))) {
@@ -281,7 +283,7 @@ static void append_tune_cache(const phia_problem* p, int R, const Geometry& g, d
     FILE* f = std::fopen(path, "a");
     if (!f) return;
     std::fprintf(f, "phia-tune4 %d %d %d %d %d %d %d %d %d %.3f\n", p->path, p->Np, R, g.kind,
-                 g.kind == 4 ? g.rows : g.mt, g.cbw, g.G,
+                 g.kind == 4 || g.kind == 6 ? g.rows : g.mt, g.cbw, g.G,
                  g.j_lds, g.xcd_map, us);
     std::fclose(f);
 }
@@ -427,6 +429,52 @@ static bool make_geometry_res(phia_problem* p, int R, Geometry& g)
     return true;
 }
 
+// Split sweep (k_sweep_split): a group of G workgroups (0: as few as hold the
+// columns) per block of `rows` replicas (4 or 16; 0: the fewest with which
+// every block runs at once).  False if it does not apply.
+static bool make_geometry_split(phia_problem* p, int R, int rows, int G, Geometry& g)
+{
+    const int planes = p->path == PHIA_PATH_I8 ? 1 : p->path == PHIA_PATH_BF16HILO ? 2 : p->path == PHIA_PATH_FP32 ? 3 : 0;
+    if (!planes || p->no_split || p->trace || p->one_block_kernel || p->mh || p->ikick || p->maxrow >= kSplitMaxRow)
+        return false;
+    if (planes > 1 && p->maxabsJ > (planes == 2 ? kSplitMaxJ2 : kSplitMaxJ3)) return false;
+    const int waves = split_waves(p->Np, planes), ncb = p->Np / 16;
+    if (waves == 0) return false;
+    const int fewest = std::max(2, (ncb + waves - 1) / waves);
+    if (G != 0 && (G < fewest || G > ncb)) return false;
+    for (const int r : {4, 16}) {
+        if (rows != 0 && r != rows) continue;
+        const size_t lds = sweep_split_lds_bytes(p->Np, planes, r);
+        if (lds == 0) continue;
+        // groups in multiples of eight, every one on one XCD (the exchange
+        // stays in its L2); what is left over of the last eight exits at once
+        const int nblocks = (R + r - 1) / r, eights = (nblocks + 7) / 8;
+        const int most = max_coresident_split(p->Np, planes, r) / 8;  // workgroups per XCD
+        int m = G != 0 ? G : fewest;
+        // four replicas to a group leave the CUs idle otherwise: fewer columns
+        // per member (N = 2000, 16 replicas, 32 members 1.62 us per step, 16
+        // members 2.14; N = 500 in three planes, 128 replicas, 8 members 1.45,
+        // 4 members 1.63)
+        while (G == 0 && r == 4 && 2 * m <= ncb && eights * 2 * m <= most) m *= 2;
+        const int groups = most / m * 8;
+        if (groups == 0 || (rows == 0 && r != 16 && nblocks > groups)) continue;
+        g = Geometry{};
+        g.ok = true;
+        g.kind = 6;
+        g.planes = planes;
+        g.mt = 1;
+        g.cbw = 1;
+        g.G = m;
+        g.rows = r;
+        g.nblocks = nblocks;
+        g.ngroups = std::min(8 * eights, groups);
+        g.xcd_map = 1;
+        g.lds = lds;
+        return true;
+    }
+    return false;
+}
+
 // Replica counts that take the VALU sweeps by default.
 constexpr int kValuTuneMaxR = 64;  // the autotuner also times the int8 VALU sweep up to here
 
@@ -519,6 +567,8 @@ static std::vector<Geometry> candidate_geometries(phia_problem* p, int R)
     {
         Geometry g;
         if (make_geometry_res(p, R, g)) out.push_back(g);
+        for (const int rows : {4, 16})
+            if (make_geometry_split(p, R, rows, 0, g)) out.push_back(g);
     }
     if (p->path == PHIA_PATH_I8 && R <= kValuTuneMaxR)
         for (int rb : {1, 2}) {
@@ -602,6 +652,12 @@ static void choose_geometry(phia_problem* p, int R)
             if (make_geometry_res(p, R, g)) p->geo = g;
             return;
         }
+        if (std::strncmp(env, "split", 5) == 0) {
+            Geometry g;
+            (void)std::sscanf(env, "split,%d,%d", &f_mt, &f_G);
+            if (make_geometry_split(p, R, f_mt, f_G, g)) p->geo = g;
+            return;
+        }
         if (std::sscanf(env, "valu,%d", &f_G) == 1) {
             Geometry g;
             if (make_geometry_valu(p, R, f_G, g)) p->geo = g;
@@ -621,7 +677,9 @@ static void choose_geometry(phia_problem* p, int R)
         }
     }
     if (p->tuned.ok && p->tuned_R == R) {
-        if (p->tuned.mh == p->mh && p->tuned.kind != 0) {
+        if (p->tuned.kind == 6) {  // as far as it applies to this anneal
+            if (make_geometry_split(p, R, p->tuned.rows, p->tuned.G, p->geo)) return;
+        } else if (p->tuned.mh == p->mh && p->tuned.kind != 0) {
             p->geo = p->tuned;
             return;
         }
@@ -636,6 +694,7 @@ static void choose_geometry(phia_problem* p, int R)
     }
     if (lookup_tune_cache(p, R)) return;
     if (p->path == PHIA_PATH_FP32 || p->path == PHIA_PATH_ELL) {
+        if (make_geometry_split(p, R, 0, 0, p->geo)) return;  // FP32
         make_geometry_valu(p, R, p->path == PHIA_PATH_FP32 ? kFp32Rows : ell_rows(R), p->geo);
         return;
     }
@@ -643,6 +702,15 @@ static void choose_geometry(phia_problem* p, int R)
         return;
     // Couplings that one CU holds: the resident sweep (resident_wins).
     if (resident_wins(p, R) && make_geometry_res(p, R, p->geo)) return;
+    // The split sweep wherever it applies, int8 only past the sizes of the
+    // resident sweep (us per step, the best of the others / it, 16 to 2048
+    // replicas): FP32 N = 32 3.4 / 1.3-1.5, N = 500 32-69 / 1.4-4.2; BF16
+    // hi/lo N = 200 4.2-4.5 / 1.3-1.9, N = 1000 5.7-19 / 1.5-9.6; int8
+    // N = 513 2.8-7.9 / 1.3-6.4, N = 900 2.6-11.9 / 1.3-8.9, N = 2000
+    // 5.2-17.5 / 1.6-12.3.  BF16 hi/lo up to 128 columns keeps one workgroup
+    // per block, which needs no exchange (N = 64 1.25 / 1.29 at 16 replicas,
+    // 1.36 / 2.9 at 4096).
+    if (p->Np > (p->path == PHIA_PATH_BF16HILO ? 128 : 512) && make_geometry_split(p, R, 0, 0, p->geo)) return;
     // Few replicas on the int8 path: the VALU dot-product sweep.
     if (p->path == PHIA_PATH_I8 && R <= valu_fallback(p->Np) && make_geometry_valu(p, R, valu_rows(R), p->geo))
         return;
@@ -654,11 +722,11 @@ static void choose_geometry(phia_problem* p, int R)
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->dev) != hipSuccess || cus < 1) cus = 256;
     int min_iters = 1 << 30;
     for (const Geometry& g : cands)
-        if (g.kind != 4 && g.kind != 5) min_iters = std::min(min_iters, (g.nblocks + g.ngroups - 1) / g.ngroups);
+        if (g.kind < 4) min_iters = std::min(min_iters, (g.nblocks + g.ngroups - 1) / g.ngroups);
     double best = 0;
     for (const Geometry& g : cands) {
         const int iters = (g.nblocks + g.ngroups - 1) / g.ngroups;
-        if (iters != min_iters || g.kind == 4 || g.kind == 5) continue;  // those: by the rules above or tuning only
+        if (iters != min_iters || g.kind >= 4) continue;  // those: by the rules above or tuning only
         const int cbs_max = (p->Np / 16 + g.G - 1) / g.G;
         const double elems = static_cast<double>(g.rows) * cbs_max * 16;
         double cost = g.kind >= 1 ? 1e6 + 2 * g.G - (g.kind == 2 ? 1 : 0) + (g.j_lds ? 0 : 0.5)
@@ -753,8 +821,9 @@ void release_resident(phia_problem* p)
 
 // Launch geometry that an anneal of R replicas without the accept/reject
 // step or energy traces would take (forced, tuned, cached or default), with
-// the problem's current anneal left as it is.
-Geometry plain_geometry(phia_problem* p, int R, int ikick)
+// the problem's current anneal left as it is; split = false leaves out the
+// split sweep.
+Geometry plain_geometry(phia_problem* p, int R, int ikick, bool split)
 {
     const Geometry saved = p->geo;
     const int mh = p->mh, ik = p->ikick;
@@ -762,7 +831,9 @@ Geometry plain_geometry(phia_problem* p, int R, int ikick)
     p->mh = 0;
     p->ikick = ikick;
     p->trace = false;
+    p->no_split = !split;
     choose_geometry(p, R);
+    p->no_split = false;
     const Geometry g = p->geo;
     p->geo = saved;
     p->mh = mh;
@@ -1232,7 +1303,8 @@ phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps, 
         return fail(PHIA_ERANGE, "no kernel geometry fits N = %d on this device", p->N);
     }
     if (p->geo.G > 1) {
-        // Tagged exchange words start at zero; tags start at 1.
+        // Tagged exchange words start at zero; tags start at 1 (the split
+        // sweep's partial energies travel in them).
         const size_t xb = 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.rows * (p->Np / 16) * sizeof(uint64_t);
         const size_t pb = 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.G * p->geo.rows * 2 * sizeof(uint64_t);
         if ((e = dalloc(reinterpret_cast<void**>(&p->dxbits), xb, cnt)) != hipSuccess ||
@@ -1291,6 +1363,24 @@ phia_status phia_anneal_run(phia_problem* p, int64_t k_end)
     if (k_end == p->k) return PHIA_OK;
     hipError_t e = hipSetDevice(p->dev);
     if (e != hipSuccess) return hip_fail(p, e, "hipSetDevice");
+    if (p->geo.kind == 6 && p->st && !p->give_up) {
+        // Under stream capture the launches are recorded, and a replay would
+        // meet the tags of the launch before it: where there is a sweep
+        // without an exchange for this shape, that one is recorded.
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(p->st, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive) {
+            const Geometry split = p->geo;
+            p->no_split = true;
+            choose_geometry(p, p->R);
+            p->no_split = false;
+            if (p->geo.ok && p->geo.G == 1) {
+                st = phia_anneal_run(p, k_end);
+                p->geo = split;
+                return st;
+            }
+            p->geo = split;
+        }
+    }
     SweepArgs a = sweep_args(p);
     a.k0 = p->k;
     a.k1 = k_end;
@@ -1303,6 +1393,25 @@ phia_status phia_anneal_run(phia_problem* p, int64_t k_end)
         e = launch_sweep_res(p->geo.fp4, a, p->st);
     } else if (p->geo.kind == 4) {
         e = launch_sweep_valu(valu_form(p), p->geo.rows, p->geo.j_lds != 0, a, p->st);
+    } else if (p->geo.kind == 6) {
+        // 16-bit tags.  Groups that run every pass rewrite their words in
+        // turn, so any run of sequence numbers will do; words of a group
+        // that sat out the last pass must not meet their own tag again.
+        const int64_t iters = (p->geo.nblocks + p->geo.ngroups - 1) / p->geo.ngroups;
+        const bool uneven = iters > 1 && p->geo.nblocks % p->geo.ngroups != 0;
+        const int64_t chunk = std::max<int64_t>(1, (int64_t(1) << 30) / iters);
+        for (int64_t k = p->k; k < k_end && e == hipSuccess;) {
+            if (uneven && p->seq > 0xfff0u) {
+                if ((e = clear_exchange(p)) != hipSuccess) break;
+                p->seq = 0;
+            }
+            a.k0 = k;
+            a.k1 = std::min(k_end, k + chunk);
+            a.seq_base = p->seq;
+            e = launch_sweep_split(a, p->geo.planes, p->st);
+            p->seq += static_cast<uint32_t>(iters * (a.k1 - a.k0 + 1));
+            k = a.k1;
+        }
     } else if (p->geo.kind >= 1) {
         // 24-bit tags: launches of at most `chunk` steps, and the sequence
         // restarts (with cleared words) before it would wrap.
@@ -1633,7 +1742,7 @@ phia_status phia_autotune(phia_problem* p, int32_t replicas, int64_t probe_steps
     // the best one cannot win; skip them.
     int min_iters = 1 << 30;
     for (const Geometry& g : cands)
-        if (g.kind != 5) min_iters = std::min(min_iters, (g.nblocks + g.ngroups - 1) / g.ngroups);
+        if (g.kind < 5) min_iters = std::min(min_iters, (g.nblocks + g.ngroups - 1) / g.ngroups);
     hipError_t e = hipSetDevice(p->dev);
     if (e != hipSuccess) return hip_fail(p, e, "hipSetDevice");
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1648,7 +1757,7 @@ phia_status phia_autotune(phia_problem* p, int32_t replicas, int64_t probe_steps
     Geometry best{};
     double best_step_us = 0.0;
     for (const Geometry& g : cands) {
-        if ((g.nblocks + g.ngroups - 1) / g.ngroups > 2 * min_iters) continue;
+        if (g.kind < 5 && (g.nblocks + g.ngroups - 1) / g.ngroups > 2 * min_iters) continue;
         free_state(p);
         p->tuned = g;
         p->tuned_R = replicas;
@@ -1746,7 +1855,7 @@ phia_status phia_set_exchange_seq(phia_problem* p, uint32_t seq)
     if (st != PHIA_OK) return st;
     if (!p->started) return fail(PHIA_ESTATE, "phia_anneal_start has not been called");
     if (p->geo.G < 2) return fail(PHIA_ESTATE, "the current geometry has no exchange between workgroups");
-    const uint32_t room = p->geo.kind >= 1 ? (1u << 24) - 2u : 0xfffffffeu;
+    const uint32_t room = p->geo.kind == 6 ? 0xfff0u : p->geo.kind >= 1 ? (1u << 24) - 2u : 0xfffffffeu;
     if (seq > room) return fail(PHIA_EINVAL, "seq = %u beyond the tag range", seq);
     p->seq = seq;
     return PHIA_OK;
