@@ -98,7 +98,7 @@ typedef enum { PHIA_DERIV_TANH = 0, PHIA_DERIV_POLY2 = 1 } phia_deriv;
  * mh_up (accepted) or mh_down (rejected) and clamped to [2^-10, 2^10]; lam
  * scales beta in the kick as well (c_k lam).  mh_up = mh_down = 1 keeps the
  * schedule fixed.  metropolis = 0 ignores mh_up and mh_down.  Metropolis runs
- * use the one-block-per-workgroup sweep (never the interleaved one). */
+ * use the resident and VALU sweeps and the one-block-per-workgroup sweep. */
 typedef struct {
     float beta0, beta1;
     const float* betas;

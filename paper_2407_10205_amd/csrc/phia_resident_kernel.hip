@@ -24,6 +24,8 @@
 // energy sums to LDS, barrier) at small N, then instruction issue: at N = 800
 // each SIMD issues four waves' 91 products of 16 cycles and 13 kicks of about
 // 60 instructions per step.  A quarter of the matrix-core rows is used.
+// Accept/reject step (L = 25), the column split / this: N = 64, 256 replicas
+// 2.0 / 0.52 us per step, N = 500 4.1 / 1.23, N = 800 4.6 / 2.6.
 //
 // Operands: FP4 couplings and spins (v_mfma_scale_f32_16x16x128_f8f6f4, FP32
 // accumulation of integers below 2^24: exact) or int8 (v_mfma_i32_16x16x64_i8).
@@ -44,9 +46,17 @@ namespace {
 constexpr int kResWaves = 16;
 constexpr int kResRows = 4;  // replicas per workgroup
 
-// Row energies [3][4] int32 or float, then [2 parities][4 rows][stride] spins,
-// then the coupling fragments of the blocks past the resident ones.
-constexpr uint32_t kResFixed = 64;
+// Row energies [3][4] int32 or float; the accept/reject step's state (ResMh);
+// then [2 parities][4 rows][stride] spins and the coupling fragments of the
+// blocks past the resident ones.
+struct ResMh {
+    unsigned long long q[8];   // kinetic units at the trajectory's end [4], start [4]
+    int64_t Es[4], El[4];      // energy at the trajectory's start, of the last step before this launch
+    float lam[4];              // beta multipliers
+    int32_t out[4], acc[4], dec[4];
+};
+constexpr uint32_t kResMh = 64, kResFixed = 256;
+static_assert(kResMh + sizeof(ResMh) <= kResFixed, "LDS head");
 __host__ __device__ inline uint32_t res_srow(int nkb) { return 64u * static_cast<uint32_t>(nkb) + 16u; }
 __host__ __device__ inline uint32_t res_sbytes(int nkb) { return 2u * kResRows * res_srow(nkb); }
 
@@ -66,7 +76,21 @@ __device__ __attribute__((noinline)) Draws res_draws(uint64_t seed, uint64_t rep
     return Draws{{g[0], g[1], g[2], g[3]}};
 }
 
-template <bool FP4, int CB, int CBV, int NKB, int DERIV>
+// The decision of one replica and its multiplier after it; a call for the
+// same reason.
+struct Decision {
+    int out;
+    float lam;
+};
+__device__ __attribute__((noinline)) Decision res_decide(uint64_t seed, uint64_t rs, int64_t traj, int64_t Es, int64_t Ee,
+                                                         int64_t dq, float beta, float lam, float sigma, float up,
+                                                         float down)
+{
+    const int out = mh_outcome(seed, rs, traj, Es, Ee, dq, beta, lam, sigma);
+    return Decision{out, mh_lambda(lam, out, up, down)};
+}
+
+template <bool FP4, int CB, int CBV, int NKB, int DERIV, bool MH>
 __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(4))) k_sweep_res(SweepArgs a)
 {
     static_assert(CB <= 4, "one lane pair per generator block");
@@ -139,12 +163,19 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
         }
         bK = a.bestStep[rep];
     }
-    // the kick's constants in VGPRs, unless the couplings need the registers
-    // (N = 800: 2.43 us per step with them, their spills in the step, 1.99 without)
+    // the kick's constants (and multiplier) in VGPRs, unless the couplings need
+    // the registers (N = 800: 2.43 us per step with them, their spills in the
+    // step, 1.99 without; accept/reject 2.79 and 2.58)
     constexpr bool kHeld = CBV * NKB <= 10;
     const float eps = kHeld ? in_vgpr(a.eps) : a.eps, gamma = kHeld ? in_vgpr(a.gamma) : a.gamma;
     Sech2K sk{};
     if constexpr (DERIV == 0 && kHeld) sk = sech2_in_vgprs();
+    // accept/reject: the first lane of a replica's row in wave 0 decides
+    ResMh* const sM = reinterpret_cast<ResMh*>(lds + kResMh);
+    const bool judge = MH && wave == 0 && lr == 0 && rok;
+    float lam = 1.0f;  // kHeld: the replica's multiplier
+    if (MH && rok) lam = a.lam[rep];
+    if (MH && tid < 4) sM->lam[tid] = 1.0f;
     const int64_t L = a.L;
     int64_t next_ref = a.k0 + (L - a.k0 % L) % L;
     uint64_t round = static_cast<uint64_t>(next_ref / L);
@@ -156,6 +187,15 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
     const bool writer = !FP4 || (lr & 4) == 0;
     const unsigned char* const arow = sS + static_cast<uint32_t>(lr >> 2) * srow + 16 * lg;
     __syncthreads();
+    if (judge) {
+        sM->q[4 + lg] = a.k0 > 0 ? static_cast<unsigned long long>(a.mhQ[rep]) : 0ull;
+        sM->Es[lg] = a.mhE[rep * 2];
+        sM->El[lg] = a.mhE[rep * 2 + 1];
+        sM->lam[lg] = lam;
+        sM->acc[lg] = a.mhc[rep * 2];
+        sM->dec[lg] = a.mhc[rep * 2 + 1];
+    }
+    if constexpr (MH) __syncthreads();
 
     // The steps, for a wave with NB column blocks (its last one may be past
     // the end; the same barriers in either copy).
@@ -195,12 +235,53 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
             }
         };
 
+        // energy of a replica from its sum (which is even)
+        auto energy = [&](int slot) -> int64_t {
+            return FP4 ? static_cast<int64_t>(-0.5f * sEf[slot]) : -(sEi[slot] >> 1);
+        };
+        // kinetic units of the lane's replica, added up in q[at]
+        auto kinetic = [&](int at) {
+            long long q = 0;
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+                if (rok && cbt(i) * 16 + lr < N) q += kin_units(x[i], v[i]);
+            q = wave_sum16_i64(q);
+            if (lr == 0) atomicAdd(sM->q + at + lg, static_cast<unsigned long long>(q));
+        };
         const ConstF ctab = scalar_table(a.ctab);
         int r3 = static_cast<int>(a.k0 % 3);
         for (int64_t k = a.k0; k < a.k1; ++k) {
             const int r3p = (r3 == 0) ? 2 : r3 - 1, r3n = (r3 == 2) ? 0 : r3 + 1;
             const float ck_s = ctab[k];
             if (k == next_ref) {  // momentum refresh
+                if (MH && k > 0) {
+                    // End of a trajectory: one decision per replica, and x back
+                    // to the trajectory's start where it was rejected.
+                    kinetic(0);
+                    __syncthreads();  // the kinetic units, the energy sums of step k - 1
+                    if (judge) {
+                        const int64_t Ee = k > a.k0 ? energy(r3p * 4 + lg) : sM->El[lg];
+                        const Decision d = res_decide(a.seed, static_cast<uint64_t>(a.r_base + rep), k / L - 1, sM->Es[lg],
+                                                      Ee, static_cast<int64_t>(sM->q[lg] - sM->q[4 + lg]),
+                                                      a.btab[k - 1], sM->lam[lg], a.sigma, a.mh_up, a.mh_down);
+                        sM->out[lg] = d.out;
+                        sM->lam[lg] = d.lam;
+                        if (d.out != 0) sM->Es[lg] = Ee;
+                        if (d.out >= 0) {
+                            sM->acc[lg] += d.out;
+                            sM->dec[lg] += 1;
+                        }
+                        sM->q[lg] = sM->q[4 + lg] = 0;
+                    }
+                    __syncthreads();
+                    if (rok) {
+                        lam = sM->lam[lg];
+                        if (sM->out[lg] == 0)
+#pragma unroll
+                            for (int i = 0; i < NB; ++i)
+                                if (cbt(i) * 16 + lr < N) x[i] = a.x0[rep * Np + cbt(i) * 16 + lr];
+                    }
+                }
                 const int b = lane >> 1, bi = b >> 3;  // block: column block bi, replica (b >> 1) & 3, half b & 1
                 const Draws d = res_draws(a.seed, static_cast<uint64_t>(a.r_base + static_cast<int64_t>(blockIdx.x) * kResRows + ((b >> 1) & 3)),
                                           round, static_cast<uint64_t>(wave + W * bi) * 2 + (b & 1), lane & 1);
@@ -215,6 +296,12 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
                 }
                 ++round;
                 next_ref += L;
+                if constexpr (MH) {  // start of a trajectory
+#pragma unroll
+                    for (int i = 0; i < NB; ++i)
+                        if (rok && cbt(i) * 16 + lr < N) a.x0[rep * Np + cbt(i) * 16 + lr] = x[i];
+                    kinetic(4);
+                }
             }
             // Drift and readout.
             unsigned char* S = sS + static_cast<uint32_t>(k & 1) * sbuf;
@@ -290,7 +377,7 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
                 part = row_sum16_dpp(part);
                 if (lr == 0) atomicAdd(sEi + slot, part);
             }
-            const float ck = in_vgpr(ck_s);
+            const float ck = MH ? ck_s * (kHeld ? lam : sM->lam[lg]) : in_vgpr(ck_s);
             float xn[NB], vn[NB];
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
@@ -323,6 +410,15 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
         a.v[rep * Np + col] = v[i];
         a.bestS[rep * Np + col] = ((best >> i) & 1u) ? 1 : -1;
     }
+    if (judge) {
+        const int slot = static_cast<int>((a.k1 - 1) % 3) * 4 + lg;
+        a.mhE[rep * 2] = sM->Es[lg];
+        a.mhE[rep * 2 + 1] = FP4 ? static_cast<int64_t>(-0.5f * sEf[slot]) : -(sEi[slot] >> 1);
+        a.mhQ[rep] = static_cast<int64_t>(sM->q[4 + lg]);
+        a.lam[rep] = sM->lam[lg];
+        a.mhc[rep * 2] = sM->acc[lg];
+        a.mhc[rep * 2 + 1] = sM->dec[lg];
+    }
     if (wave == 0 && lr == 0 && rok) {
         if constexpr (FP4)
             a.bestE[rep] = bEf == __builtin_inff() ? INT64_MAX : static_cast<int64_t>(bEf);
@@ -334,16 +430,19 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
 
 // One variant's kernel; columns blocks up to 16 CB, k blocks up to NKB.
 template <bool FP4, int CB, int CBV, int NKB>
-const void* res_kernel(int deriv)
+const void* res_kernel(int deriv, int mh)
 {
-    return deriv ? reinterpret_cast<const void*>(k_sweep_res<FP4, CB, CBV, NKB, 1>)
-                 : reinterpret_cast<const void*>(k_sweep_res<FP4, CB, CBV, NKB, 0>);
+    if (mh)
+        return deriv ? reinterpret_cast<const void*>(k_sweep_res<FP4, CB, CBV, NKB, 1, true>)
+                     : reinterpret_cast<const void*>(k_sweep_res<FP4, CB, CBV, NKB, 0, true>);
+    return deriv ? reinterpret_cast<const void*>(k_sweep_res<FP4, CB, CBV, NKB, 1, false>)
+                 : reinterpret_cast<const void*>(k_sweep_res<FP4, CB, CBV, NKB, 0, false>);
 }
 
 struct ResVariant {
     bool fp4;
     int max_ncb, cbv, nkb;
-    const void* (*kernel)(int deriv);
+    const void* (*kernel)(int deriv, int mh);
 };
 // Coupling fragments in VGPRs: at most 16 per wave (64 registers); what is
 // past the first cbv blocks per wave must fit the LDS.
@@ -388,7 +487,7 @@ hipError_t launch_sweep_res(int fp4, const SweepArgs& a, hipStream_t st)
     const size_t lds = sweep_res_lds_bytes(a.N, fp4);
     const ResVariant* v = res_variant(a.N, fp4);
     if (lds == 0 || a.R < 1 || a.k1 <= a.k0) return hipErrorInvalidValue;
-    const void* kern = v->kernel(a.deriv ? 1 : 0);
+    const void* kern = v->kernel(a.deriv ? 1 : 0, a.mh);
     if (lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
         if (e != hipSuccess) return e;

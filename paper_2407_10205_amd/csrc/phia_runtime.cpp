@@ -410,7 +410,7 @@ static bool make_geometry_pp(phia_problem* p, int R, int G, int fp4, Geometry& g
 // not apply.
 static bool make_geometry_res(phia_problem* p, int R, Geometry& g)
 {
-    if (p->path != PHIA_PATH_I8 || p->one_block_kernel || p->mh || p->ikick) return false;
+    if (p->path != PHIA_PATH_I8 || p->one_block_kernel || p->ikick) return false;
     const int64_t row = 2 * p->maxrow * p->N;  // bounds |sum_i s_i (I_i + h_i)|
     const int fp4 = p->has_j4 && row < (int64_t(1) << 24) && sweep_res_lds_bytes(p->N, 1) > 0;
     if (!fp4 && (row >= (int64_t(1) << 31) || sweep_res_lds_bytes(p->N, 0) == 0)) return false;
@@ -426,6 +426,7 @@ static bool make_geometry_res(phia_problem* p, int R, Geometry& g)
     g.nblocks = (R + g.rows - 1) / g.rows;
     g.ngroups = g.nblocks;
     g.lds = sweep_res_lds_bytes(p->N, fp4);
+    g.mh = p->mh;
     return true;
 }
 
