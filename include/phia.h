@@ -140,7 +140,7 @@ typedef struct {
                                with FP4 operands); 6: the split sweep, columns of
                                4 or 16 replicas over a group of workgroups with
                                the couplings in registers as int8 planes (FP32,
-                               BF16HILO, I8, Np <= 2048)                        */
+                               BF16HILO, I8, Np <= 2048) or ELL slots           */
     int64_t steps;          /* T of the current anneal                               */
     int64_t step;           /* next step to run                                      */
     int64_t max_abs_J;      /* max |J| in units                                      */
@@ -208,7 +208,7 @@ int32_t phia_valu_crossover(int32_t Np);
  * Enqueued on the problem's stream; returns without waiting.  The sweep's
  * launch geometry is fixed here from (path, Np, replicas): on the I8 path,
  * couplings that one CU holds run the resident sweep (sweep_kernel 5); larger
- * ones, FP32 and 16-bit couplings the split sweep (6); the accept/reject step,
+ * ones, FP32, 16-bit and sparse couplings the split sweep (6); the accept/reject step,
  * energy traces and Np > 2048 the other sweeps.
  * A tuned or cached geometry (phia_autotune) takes precedence. */
 phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps,

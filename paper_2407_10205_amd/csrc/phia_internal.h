@@ -99,13 +99,14 @@ size_t sweep_res_lds_bytes(int N, int fp4);
 hipError_t launch_sweep_res(int fp4, const SweepArgs& a, hipStream_t st);
 // Split sweep (k_sweep_split): 4 or 16 replicas per group of G workgroups of
 // split_waves() column blocks each, the couplings as `planes` int8 planes (I8: 1,
-// BF16 hi/lo: 2, FP32: 3) in VGPRs.  0: no variant for Np columns.
+// BF16 hi/lo: 2, FP32: 3) in VGPRs, or as `slots` ELL slots per row (planes = 0,
+// four replicas only).  0: no variant for Np columns.
 constexpr int64_t kSplitMaxRow = 1 << 24;  // max_i(sum_j |J_ij| + |h_i|) below it
 constexpr int64_t kSplitMaxJ2 = 32639, kSplitMaxJ3 = 8355711;  // |J| that two and three planes hold
 int split_waves(int Np, int planes);
-size_t sweep_split_lds_bytes(int Np, int planes, int rows);
+size_t sweep_split_lds_bytes(int Np, int planes, int rows, int slots);
 hipError_t launch_sweep_split(const SweepArgs& a, int planes, hipStream_t st);
-int max_coresident_split(int Np, int planes, int rows);
+int max_coresident_split(int Np, int planes, int rows, int slots);
 hipError_t launch_sweep_mfma(int path, int mt, int cbw, const SweepArgs& a, size_t lds_bytes, hipStream_t st);
 size_t sweep_mfma_lds_bytes(int path, int mt, const SweepArgs& a);
 // out: (energy, replica, *err or 0), then with bestS the winner's n spins at byte 64

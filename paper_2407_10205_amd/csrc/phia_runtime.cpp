@@ -436,7 +436,7 @@ static bool make_geometry_res(phia_problem* p, int R, Geometry& g)
 static bool make_geometry_split(phia_problem* p, int R, int rows, int G, Geometry& g)
 {
     const int planes = p->path == PHIA_PATH_I8 ? 1 : p->path == PHIA_PATH_BF16HILO ? 2 : p->path == PHIA_PATH_FP32 ? 3 : 0;
-    if (!planes || p->no_split || p->trace || p->one_block_kernel || p->mh || p->ikick || p->maxrow >= kSplitMaxRow)
+    if (p->no_split || p->trace || p->one_block_kernel || p->mh || p->ikick || p->maxrow >= kSplitMaxRow)
         return false;
     if (planes > 1 && p->maxabsJ > (planes == 2 ? kSplitMaxJ2 : kSplitMaxJ3)) return false;
     const int waves = split_waves(p->Np, planes), ncb = p->Np / 16;
@@ -445,12 +445,12 @@ static bool make_geometry_split(phia_problem* p, int R, int rows, int G, Geometr
     if (G != 0 && (G < fewest || G > ncb)) return false;
     for (const int r : {4, 16}) {
         if (rows != 0 && r != rows) continue;
-        const size_t lds = sweep_split_lds_bytes(p->Np, planes, r);
+        const size_t lds = sweep_split_lds_bytes(p->Np, planes, r, p->ell_d);
         if (lds == 0) continue;
         // groups in multiples of eight, every one on one XCD (the exchange
         // stays in its L2); what is left over of the last eight exits at once
         const int nblocks = (R + r - 1) / r, eights = (nblocks + 7) / 8;
-        const int most = max_coresident_split(p->Np, planes, r) / 8;  // workgroups per XCD
+        const int most = max_coresident_split(p->Np, planes, r, p->ell_d) / 8;  // workgroups per XCD
         int m = G != 0 ? G : fewest;
         // four replicas to a group leave the CUs idle otherwise: fewer columns
         // per member (N = 2000, 16 replicas, 32 members 1.62 us per step, 16
@@ -563,6 +563,8 @@ static std::vector<Geometry> candidate_geometries(phia_problem* p, int R)
             Geometry g;
             if (make_geometry_valu(p, R, rb, g)) out.push_back(g);
         }
+        Geometry g;
+        if (make_geometry_split(p, R, 4, 0, g)) out.push_back(g);
         return out;
     }
     {
@@ -695,7 +697,16 @@ static void choose_geometry(phia_problem* p, int R)
     }
     if (lookup_tune_cache(p, R)) return;
     if (p->path == PHIA_PATH_FP32 || p->path == PHIA_PATH_ELL) {
-        if (make_geometry_split(p, R, 0, 0, p->geo)) return;  // FP32
+        // FP32 always (figures below).  ELL as long as every block runs at once,
+        // and from 513 to 1024 columns with at most eight column blocks to a
+        // member; the VALU sweep, one replica to a CU, is quick there (3-regular
+        // rows, us per step, VALU / split: N = 1000 1.55 / 1.36 at 64 replicas,
+        // 1.61 / 1.95 at 256; N = 2000 2.0 / 1.4-2.0 up to 128; N = 4000 3.5 /
+        // 1.5 at 32, 3.5 / 2.05 at 64; two passes, 128 replicas, 3.7 / 4.2).
+        if (make_geometry_split(p, R, 0, 0, p->geo)) {
+            if (p->path == PHIA_PATH_FP32 || p->Np > 1024 || (p->Np > 512 && p->Np / 16 <= 8 * p->geo.G)) return;
+            p->geo = Geometry{};
+        }
         make_geometry_valu(p, R, p->path == PHIA_PATH_FP32 ? kFp32Rows : ell_rows(R), p->geo);
         return;
     }

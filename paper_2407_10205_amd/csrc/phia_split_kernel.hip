@@ -9,6 +9,9 @@
 // the exact integer field of every other path, at a quarter of the register
 // space and of the matrix-core time of FP32, half of BF16 hi/lo.
 //
+// Sparse rows (ELL path, PL = 0) keep their slots in LDS instead, the first
+// four of a column in VGPRs, and gather one spin byte per slot.
+//
 // Layout.  NW waves, one 16-column block each, its fragments (planes x k
 // blocks, at most 36 with eight waves and 96 with four) in VGPRs for the
 // whole launch.  FEW: four replicas per group, spins as the A operand with
@@ -41,7 +44,8 @@
 // block and plane the products (N = 2000, four replicas, 1.6 us; sixteen,
 // 2.9 us).  us per step, the sweeps it took the place of / this: N = 500 FP32,
 // 128 replicas 31.7 / 1.50; N = 1000 BF16 hi/lo, 128 replicas 12.1 / 1.95;
-// N = 2000 int8, 16 replicas 5.2 / 1.63, 512 replicas 8.6 / 6.2.
+// N = 2000 int8, 16 replicas 5.2 / 1.63, 512 replicas 8.6 / 6.2; 3-regular
+// N = 4000, 32 replicas 3.5 / 1.55, 64 replicas 3.54 / 2.05.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -61,6 +65,7 @@ constexpr uint32_t kSplitMask = 384, kSplitAbort = 392, kSplitFar = 396, kSplitS
 __host__ __device__ inline uint32_t split_srow(int nkb) { return 64u * static_cast<uint32_t>(nkb) + 16u; }
 
 constexpr int kSplitDepth = 4;  // spin fragments in flight
+constexpr int kSplitSlots = 4;  // ELL slots of a column in VGPRs
 
 __device__ __forceinline__ v4i pack16(const int (&c)[16])
 {
@@ -177,12 +182,26 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW
     unsigned char* sS = lds + kSplitSpins;  // by step parity
     const int xcd = __builtin_amdgcn_s_getreg(20 | (3 << 11));  // XCC_ID
 
-    v4i jr[NKB][PL];
+    constexpr int PN = PL > 0 ? PL : 1, KN = PL > 0 ? NKB : 1;
+    v4i jr[KN][PN];
+    int32_t slot[kSplitSlots];  // ELL: (coupling << 16) | column
+    int32_t* const sL = reinterpret_cast<int32_t*>(sS + 2u * sbuf);  // ELL: [slots][16 NW]
+    if constexpr (PL > 0) {
 #pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
+        for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
-        for (int pl = 0; pl < PL; ++pl) jr[kb][pl] = v4i{0, 0, 0, 0};
-        if (cval && kb < nkb) load_planes<PL>(a.J, Np, cblk, kb, lane, jr[kb]);
+            for (int pl = 0; pl < PL; ++pl) jr[kb][pl] = v4i{0, 0, 0, 0};
+            if (cval && kb < nkb) load_planes<PN>(a.J, Np, cblk, kb, lane, jr[kb]);
+        }
+    } else {
+        const int32_t* E = static_cast<const int32_t*>(a.J);
+#pragma unroll
+        for (int d = 0; d < kSplitSlots; ++d)
+            slot[d] = cval && d < a.ell_d ? E[static_cast<size_t>(d) * Np + cblk * 16 + lr] : 0;
+        for (int u = tid; u < (a.ell_d - kSplitSlots) * 16 * NW; u += 64 * NW) {
+            const int d = kSplitSlots + u / (16 * NW), col = cb0 * 16 + u % (16 * NW);
+            sL[u] = col < cb1 * 16 ? E[static_cast<size_t>(d) * Np + col] : 0;
+        }
     }
     // spins of k positions past the columns meet zero couplings
     for (uint32_t u = tid; u < (kSplitSpins + 2u * sbuf) / 4u; u += 64 * NW) reinterpret_cast<uint32_t*>(lds)[u] = 0u;
@@ -322,39 +341,58 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW
                 }
                 leave = abort_flag != 0;
                 if (!closing && cval) {
-                    // A ring of spin fragments keeps the LDS reads ahead of
-                    // the products (the compiler reads two at a time and
-                    // waits for them).
-                    constexpr int D = NKB < kSplitDepth ? NKB : kSplitDepth;
-                    v4i acc[PL];
+                    float If[E];
+                    int field[E];  // J s
+                    if constexpr (PL == 0) {
+                        static_assert(PL > 0 || FEW, "ELL: four replicas per group");
+                        const int8_t* const Sg = reinterpret_cast<const int8_t*>(S + static_cast<uint32_t>(lg) * srow);
+                        int sum = 0;
 #pragma unroll
-                    for (int pl = 0; pl < PL; ++pl) acc[pl] = v4i{0, 0, 0, 0};
-                    const unsigned char* const Sr = S + static_cast<uint32_t>(FEW ? lr >> 2 : lr) * srow + 16 * lg;
-                    v4i ring[D];
-                    __builtin_amdgcn_sched_barrier(0);
+                        for (int d = 0; d < kSplitSlots; ++d) sum += (slot[d] >> 16) * static_cast<int>(Sg[slot[d] & 0xffff]);
+                        const int32_t* const Lw = sL + wave * 16 + lr;
+#pragma unroll 4
+                        for (int d = 0; d < a.ell_d - kSplitSlots; ++d) {
+                            const int32_t w = Lw[d * 16 * NW];
+                            sum += (w >> 16) * static_cast<int>(Sg[w & 0xffff]);
+                        }
+                        field[0] = sum;
+                    } else {
+                        // A ring of spin fragments keeps the LDS reads ahead of
+                        // the products (the compiler reads two at a time and
+                        // waits for them).
+                        constexpr int D = NKB < kSplitDepth ? NKB : kSplitDepth;
+                        v4i acc[PN];
 #pragma unroll
-                    for (int kb = 0; kb < D; ++kb) ring[kb] = *reinterpret_cast<const v4i*>(Sr + kb * 64);
-                    __builtin_amdgcn_sched_barrier(0);
+                        for (int pl = 0; pl < PL; ++pl) acc[pl] = v4i{0, 0, 0, 0};
+                        const unsigned char* const Sr = S + static_cast<uint32_t>(FEW ? lr >> 2 : lr) * srow + 16 * lg;
+                        v4i ring[D];
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int kb = 0; kb < NKB; ++kb) {
-                        const v4i s4 = ring[kb % D];
+                        for (int kb = 0; kb < D; ++kb) ring[kb] = *reinterpret_cast<const v4i*>(Sr + kb * 64);
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int pl = 0; pl < PL; ++pl)
-                            acc[pl] = FEW ? __builtin_amdgcn_mfma_i32_16x16x64_i8(s4, jr[kb][pl], acc[pl], 0, 0, 0)
-                                          : __builtin_amdgcn_mfma_i32_16x16x64_i8(jr[kb][pl], s4, acc[pl], 0, 0, 0);
-                        if (kb + D < NKB) {
-                            ring[kb % D] = *reinterpret_cast<const v4i*>(Sr + (kb + D) * 64);
-                            __builtin_amdgcn_sched_barrier(0);
+                        for (int kb = 0; kb < NKB; ++kb) {
+                            const v4i s4 = ring[kb % D];
+#pragma unroll
+                            for (int pl = 0; pl < PL; ++pl)
+                                acc[pl] = FEW ? __builtin_amdgcn_mfma_i32_16x16x64_i8(s4, jr[kb][pl], acc[pl], 0, 0, 0)
+                                              : __builtin_amdgcn_mfma_i32_16x16x64_i8(jr[kb][pl], s4, acc[pl], 0, 0, 0);
+                            if (kb + D < NKB) {
+                                ring[kb % D] = *reinterpret_cast<const v4i*>(Sr + (kb + D) * 64);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                        }
+#pragma unroll
+                        for (int e = 0; e < E; ++e) {
+                            field[e] = acc[PN - 1][e];
+#pragma unroll
+                            for (int pl = PL - 2; pl >= 0; --pl) field[e] = (field[e] << 8) + acc[pl][e];
                         }
                     }
-                    float If[E];
                     int q = 0;
 #pragma unroll
                     for (int e = 0; e < E; ++e) {
-                        int I = acc[PL - 1][e];
-#pragma unroll
-                        for (int pl = PL - 2; pl >= 0; --pl) I = (I << 8) + acc[pl][e];
-                        I += hj[e];
+                        const int I = field[e] + hj[e];
                         If[e] = static_cast<float>(I);
                         const int ih = I + hj[e];
                         q += x[e] >= 0.0f ? ih : -ih;
@@ -457,12 +495,17 @@ SplitVariant split_variant_of()
             {reinterpret_cast<const void*>(k_sweep_split<PL, NKB, NW, true>),
              reinterpret_cast<const void*>(k_sweep_split<PL, NKB, NW, false>)}};
 }
+template <>
+SplitVariant split_variant_of<0, 64, 16>()
+{
+    return {0, 64, 16, {reinterpret_cast<const void*>(k_sweep_split<0, 64, 16, true>), nullptr}};
+}
 const SplitVariant kSplitVariants[] = {
     split_variant_of<1, 16, 8>(), split_variant_of<1, 24, 8>(), split_variant_of<1, 32, 8>(),
     split_variant_of<2, 4, 8>(),  split_variant_of<2, 8, 8>(),  split_variant_of<2, 16, 8>(),
     split_variant_of<2, 24, 4>(), split_variant_of<2, 32, 4>(), split_variant_of<3, 4, 8>(),
     split_variant_of<3, 8, 8>(),  split_variant_of<3, 12, 8>(), split_variant_of<3, 16, 4>(),
-    split_variant_of<3, 24, 4>(), split_variant_of<3, 32, 4>(),
+    split_variant_of<3, 24, 4>(), split_variant_of<3, 32, 4>(), split_variant_of<0, 64, 16>(),
 };
 
 const SplitVariant* split_variant(int Np, int planes)
@@ -472,7 +515,11 @@ const SplitVariant* split_variant(int Np, int planes)
     return nullptr;
 }
 
-size_t split_lds(const SplitVariant& v, int rows) { return kSplitSpins + 2u * static_cast<size_t>(rows) * split_srow(v.nkb); }
+size_t split_lds(const SplitVariant& v, int rows, int slots)
+{
+    return kSplitSpins + 2u * static_cast<size_t>(rows) * split_srow(v.nkb) +
+           (v.planes == 0 ? 64u * static_cast<size_t>(v.waves) * std::max(0, slots - kSplitSlots) : 0u);
+}
 
 int split_form(int rows) { return rows == 4 ? 0 : rows == 16 ? 1 : -1; }
 
@@ -484,18 +531,18 @@ int split_waves(int Np, int planes)
     return v ? v->waves : 0;
 }
 
-size_t sweep_split_lds_bytes(int Np, int planes, int rows)
+size_t sweep_split_lds_bytes(int Np, int planes, int rows, int slots)
 {
     const SplitVariant* v = split_variant(Np, planes);
-    if (!v || split_form(rows) < 0) return 0;
-    const size_t b = split_lds(*v, rows);
+    if (!v || split_form(rows) < 0 || !v->kernel[split_form(rows)]) return 0;
+    const size_t b = split_lds(*v, rows, slots);
     return b <= static_cast<size_t>(kLdsMax) ? b : 0;
 }
 
 hipError_t launch_sweep_split(const SweepArgs& a, int planes, hipStream_t st)
 {
     const SplitVariant* v = split_variant(a.Np, planes);
-    const size_t lds = sweep_split_lds_bytes(a.Np, planes, a.rows);
+    const size_t lds = sweep_split_lds_bytes(a.Np, planes, a.rows, a.ell_d);
     if (lds == 0 || a.k1 <= a.k0 || a.k1 - a.k0 > (int64_t(1) << 30) || (a.ncb + a.G - 1) / a.G > v->waves)
         return hipErrorInvalidValue;
     const void* kern = v->kernel[split_form(a.rows)];
@@ -508,10 +555,10 @@ hipError_t launch_sweep_split(const SweepArgs& a, int planes, hipStream_t st)
     return e != hipSuccess ? e : hipGetLastError();
 }
 
-int max_coresident_split(int Np, int planes, int rows)
+int max_coresident_split(int Np, int planes, int rows, int slots)
 {
     const SplitVariant* v = split_variant(Np, planes);
-    const size_t lds = sweep_split_lds_bytes(Np, planes, rows);
+    const size_t lds = sweep_split_lds_bytes(Np, planes, rows, slots);
     if (lds == 0) return 0;
     const void* f = v->kernel[split_form(rows)];
     int dev = 0, cus = 0, per = 0;

@@ -1,5 +1,5 @@
 """The split sweep (k_sweep_split) against the oracle, bit for bit: one, two
-and three int8 planes at the edges of its variants (k blocks, waves, members
+and three int8 planes and sparse rows at the edges of its variants (k blocks, waves, members
 of a group), four and sixteen replicas per group, ragged replica counts and
 several passes over the replica blocks, launches that begin and end between
 momentum draws and past the wrap of the tags, both kick factors, the
@@ -13,7 +13,7 @@ from paper_2407_10205_amd import instances as inst
 
 pytestmark = pytest.mark.gpu
 
-FRAC = {"i8": (5, 8), "bf16hilo": (9, 16), "fp32": (12, 20)}
+FRAC = {"i8": (5, 8), "bf16hilo": (9, 16), "fp32": (12, 20), "ell": (6, 16)}
 
 
 @pytest.fixture
@@ -24,6 +24,10 @@ def geometry(monkeypatch):
 def instance(path, N, seed):
     """Fixed-point couplings that use the path's whole width."""
     f, bits = FRAC[path]
+    if path == "ell":  # uneven rows of 0 to about a dozen couplings
+        rs = np.random.default_rng(seed)
+        A = np.triu((rs.random((N, N)) < min(1.0, 4.0 / N)) * rs.integers(-2**15 + 1, 2**15, (N, N)), 1)
+        return (A + A.T) / 2.0**f, rs.integers(-300, 300, N) / 2.0**f, f
     J, h = inst.sk_gauss_fixed(N, seed, frac_bits=f, bits=bits)
     if path != "i8" and N > 3:  # the planes' extreme values
         top = {"bf16hilo": 32639, "fp32": 8355711}[path] / 2.0**f
@@ -51,7 +55,9 @@ CASES = [("i8", 5, 3, 4, 2), ("i8", 200, 7, 4, 0), ("i8", 300, 19, 16, 7), ("i8"
          ("bf16hilo", 1000, 7, 4, 8), ("bf16hilo", 1025, 4, 4, 0), ("bf16hilo", 1537, 17, 16, 0),
          ("bf16hilo", 2048, 3, 4, 32), ("fp32", 2, 1, 4, 2), ("fp32", 33, 20, 16, 0), ("fp32", 256, 5, 4, 0),
          ("fp32", 257, 17, 16, 0), ("fp32", 512, 6, 4, 32), ("fp32", 768, 4, 4, 0), ("fp32", 769, 18, 16, 0),
-         ("fp32", 1025, 3, 4, 0), ("fp32", 1537, 17, 16, 0), ("fp32", 2000, 2, 4, 0), ("fp32", 40, 2100, 16, 2)]
+         ("fp32", 1025, 3, 4, 0), ("fp32", 1537, 17, 16, 0), ("fp32", 2000, 2, 4, 0), ("fp32", 40, 2100, 16, 2),
+         ("ell", 20, 3, 4, 2), ("ell", 300, 9, 4, 0), ("ell", 700, 6, 4, 11), ("ell", 1030, 5, 4, 5), ("ell", 4000, 3, 4, 0),
+         ("ell", 2000, 140, 4, 0), ("ell", 100, 700, 4, 5)]
 
 
 @pytest.mark.parametrize("path,N,R,rows,G", CASES)
@@ -100,7 +106,7 @@ def test_split_tags_past_their_wrap(geometry, R, seq):
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("path", ["i8", "bf16hilo", "fp32"])
+@pytest.mark.parametrize("path", ["i8", "bf16hilo", "fp32", "ell"])
 def test_split_noalloc(geometry, path):
     """The allocation-free call equals phia_anneal."""
     import torch
@@ -113,7 +119,7 @@ def test_split_noalloc(geometry, path):
         return x, v, torch.zeros(R, dtype=torch.int64, device="cuda"), torch.zeros((R, Np), dtype=torch.int8, device="cuda"), \
             torch.zeros(R, dtype=torch.int64, device="cuda")
 
-    geometry("split,16")
+    geometry("split,4" if path == "ell" else "split,16")
     with P.Problem(J, h, frac_bits=f, path=path) as p:
         p.anneal(50, 60, **sched)
         assert p.info()["sweep_kernel"] == 6
@@ -197,3 +203,10 @@ def test_split_is_the_default_where_it_applies():
     assert kind(inst.sk_gauss_fixed(513, 1)[0]) == 6
     assert kind(inst.sk_pm1(897, 1)[0]) == 6
     assert kind(inst.sk_gauss_fixed(2049, 1)[0]) != 6
+    J, h = inst.regular3_pm1(600, 1)
+    assert kind(J, h) == 6 and kind(J, h, trace=True) == 4 and kind(J, h, mh=(1.0, 1.0)) == 4
+    assert kind(J, h, R=256) == 4  # more than eight column blocks to a member
+    J, h = inst.regular3_pm1(4000, 1)
+    assert kind(J, h, R=64) == 6 and kind(J, h, R=65) == 4  # more blocks than run at once
+    J, h = inst.regular3_pm1(500, 1)
+    assert kind(J, h, path="ell") == 4
