@@ -410,7 +410,12 @@ static bool make_geometry_pp(phia_problem* p, int R, int G, int fp4, Geometry& g
 // not apply.
 static bool make_geometry_res(phia_problem* p, int R, Geometry& g)
 {
-    if (p->path != PHIA_PATH_I8 || p->one_block_kernel || p->ikick) return false;
+    if (p->path != PHIA_PATH_I8 || p->ikick) return false;
+    // Served requests past the batch sizes: from 64 replicas (N = 551 and 726,
+    // 64 replicas, 100 steps, in the column-split table 0.88 ms, on two
+    // auxiliary streams 0.17 ms; smaller ones stay in the table, by which the
+    // tests reach the read-out of its error words).
+    if (p->one_block_kernel && p->Np > kBatchMaxNp && R < 64) return false;
     const int64_t row = 2 * p->maxrow * p->N;  // bounds |sum_i s_i (I_i + h_i)|
     const int fp4 = p->has_j4 && row < (int64_t(1) << 24) && sweep_res_lds_bytes(p->N, 1) > 0;
     if (!fp4 && (row >= (int64_t(1) << 31) || sweep_res_lds_bytes(p->N, 0) == 0)) return false;
@@ -430,13 +435,24 @@ static bool make_geometry_res(phia_problem* p, int R, Geometry& g)
     return true;
 }
 
+// A served request that the split sweep runs in launches of its own, one after
+// the other, beside the table launches of the others (100 steps of 64
+// replicas, ms, in the table / alone: BF16 hi/lo N = 1105 1.82 / 0.23, N = 454,
+// 258 and 187 together 1.14 / 0.42).  ELL and FP32 requests share the device
+// on the auxiliary streams instead, int8 ones up to Np = 832 run resident
+// there or in the column-split table.
+static bool served_alone(const phia_problem* p)
+{
+    return p->path == PHIA_PATH_BF16HILO || (p->path == PHIA_PATH_I8 && p->Np > 832);
+}
+
 // Split sweep (k_sweep_split): a group of G workgroups (0: as few as hold the
 // columns) per block of `rows` replicas (4 or 16; 0: the fewest with which
 // every block runs at once).  False if it does not apply.
 static bool make_geometry_split(phia_problem* p, int R, int rows, int G, Geometry& g)
 {
     const int planes = p->path == PHIA_PATH_I8 ? 1 : p->path == PHIA_PATH_BF16HILO ? 2 : p->path == PHIA_PATH_FP32 ? 3 : 0;
-    if (p->no_split || p->trace || p->one_block_kernel || p->mh || p->ikick || p->maxrow >= kSplitMaxRow)
+    if (p->no_split || p->trace || (p->one_block_kernel && !served_alone(p)) || p->mh || p->ikick || p->maxrow >= kSplitMaxRow)
         return false;
     if (planes > 1 && p->maxabsJ > (planes == 2 ? kSplitMaxJ2 : kSplitMaxJ3)) return false;
     const int waves = split_waves(p->Np, planes), ncb = p->Np / 16;
@@ -1318,14 +1334,14 @@ phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps, 
         // Tagged exchange words start at zero; tags start at 1 (the split
         // sweep's partial energies travel in them).
         const size_t xb = 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.rows * (p->Np / 16) * sizeof(uint64_t);
-        const size_t pb = 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.G * p->geo.rows * 2 * sizeof(uint64_t);
+        const size_t pb = p->geo.kind == 6 ? 0 : 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.G * p->geo.rows * 2 * sizeof(uint64_t);
         if ((e = dalloc(reinterpret_cast<void**>(&p->dxbits), xb, cnt)) != hipSuccess ||
-            (e = dalloc(reinterpret_cast<void**>(&p->dpbuf), pb, cnt)) != hipSuccess) {
+            (pb && (e = dalloc(reinterpret_cast<void**>(&p->dpbuf), pb, cnt)) != hipSuccess)) {
             free_state(p);
             return fail(PHIA_ENOMEM, "exchange buffer allocation failed");
         }
         if ((e = hipMemsetAsync(p->dxbits, 0, xb, p->st)) != hipSuccess ||
-            (e = hipMemsetAsync(p->dpbuf, 0, pb, p->st)) != hipSuccess)
+            (pb && (e = hipMemsetAsync(p->dpbuf, 0, pb, p->st)) != hipSuccess))
             return hip_fail(p, e, "exchange buffer reset");
         p->seq = 0;
     }

@@ -5,12 +5,14 @@
 // fits the memory budget next to the requests already running; its replica
 // state then stays resident until it retires.  The service thread runs
 // scheduling rounds: each round advances every running request by one chunk
-// of steps -- the column-split instances packed into one cooperative launch
-// that has the device to itself (its workgroups wait for each other), then
-// all running instances with N <= 512 in one batched launch on the service
-// stream, overlapped with the VALU sweeps (ELL, FP32, few replicas), whose
-// own launches go round-robin to three more streams -- then reads every
-// request's best energy with one synchronisation.  A request retires when its best energy reaches its
+// of steps -- the split sweeps (16-bit and the largest int8 instances) in
+// launches of their own and the other column-split instances packed into one
+// cooperative launch, each with the device to itself (their workgroups wait
+// for each other), then what is left of the instances with N <= 512 in one
+// batched launch on the service stream, overlapped with the resident (int8
+// that one CU holds) and VALU sweeps (ELL, FP32), whose own launches go round-robin to
+// three more streams -- then reads every request's best energy with one
+// synchronisation.  A request retires when its best energy reaches its
 // target or its step budget is used up; its result (energy, replica, steps,
 // best state, timestamps) is kept for the caller and its device state is
 // released, which may admit waiting requests at the next round.  Requests
@@ -73,7 +75,7 @@ struct phia_server {
     int64_t chunk = 1000;
     int dev = 0;
     hipStream_t st = nullptr;
-    static constexpr int kAux = 3;  // streams for the VALU sweeps' own launches (default priority)
+    static constexpr int kAux = 3;  // streams for the VALU and resident sweeps' own launches (default priority)
     hipStream_t aux[kAux] = {};
     hipEvent_t ev_split = nullptr;      // the cooperative launch of a round has ended
     hipEvent_t ev_aux[kAux] = {};       // an auxiliary stream's launches of a round have ended
@@ -127,32 +129,41 @@ void round_once(phia_server* s, std::vector<Request*>& run)
     const int n = static_cast<int>(run.size());
     std::vector<phia_problem*> small, split;
     std::vector<int64_t> small_end, split_end;
-    std::vector<std::pair<Request*, int64_t>> solo;  // VALU sweeps (normal launches of their own)
+    std::vector<std::pair<Request*, int64_t>> solo;  // VALU and resident sweeps (normal launches of their own)
     hipError_t e = hipSuccess;
+    // Batch-sized instances take the launches of their own kind (resident or
+    // split sweep) while they are few: 0.4-1.2 us per step each, on three
+    // streams, or 1.3-1.5 one after the other, against 2.9-3.6 (int8) and 11
+    // us (BF16 hi/lo) for the batched launch of any number of them.
+    int own[2] = {0, 0};
+    for (const Request* r : run)
+        if (r->p->Np <= kBatchMaxNp && (r->p->geo.kind == 5 || r->p->geo.kind == 6)) ++own[r->p->geo.kind - 5];
+    const bool batched[2] = {own[0] > 9, own[1] > 8};
     for (Request* r : run) {
         phia_problem* p = r->p;
         const int64_t k_end = std::min(p->k + s->chunk, p->T);
         const bool mfma = p->path == PHIA_PATH_I8 || p->path == PHIA_PATH_BF16HILO;
-        if (p->Np <= kBatchMaxNp && mfma) {
+        if (p->Np <= kBatchMaxNp && mfma &&
+            (p->geo.kind == 0 || (p->geo.kind >= 5 && batched[p->geo.kind - 5]))) {
             small.push_back(p);
             small_end.push_back(k_end);
         } else if (mfma && p->geo.kind == 0 && p->geo.G > 1) {
             split.push_back(p);
             split_end.push_back(k_end);
         } else if (k_end > p->k) {
-            if (p->geo.kind == 4)
+            if (p->geo.kind == 4 || p->geo.kind == 5)
                 solo.push_back({r, k_end});
             else if (phia_anneal_run(p, k_end) != PHIA_OK)
                 r->failed = true;
         }
     }
-    // Column-split instances: several per cooperative launch, with nothing
+    // Other column-split instances: several per cooperative launch, with nothing
     // else on the device (the launches below wait for it).
     if (!split.empty() && launch_group_chunk(split.data(), static_cast<int>(split.size()), split_end.data(), s->st,
                                              s->gtab, s->gtab_cap) != PHIA_OK)
         for (Request* r : run)
             if (std::find(split.begin(), split.end(), r->p) != split.end()) r->failed = true;
-    // The VALU sweeps' launches on the auxiliary streams, after it.
+    // The VALU and resident sweeps' launches on the auxiliary streams, after it.
     const int na = std::min<int>(phia_server::kAux, static_cast<int>(solo.size()));
     bool aux_ok = na == 0 || hipEventRecord(s->ev_split, s->st) == hipSuccess;
     for (int k = 0; aux_ok && k < na; ++k) aux_ok = hipStreamWaitEvent(s->aux[k], s->ev_split, 0) == hipSuccess;
@@ -273,7 +284,7 @@ void service(phia_server* s)
         for (Request* r : admitted) {
             r->saved_stream = r->p->st;
             r->p->st = s->st;
-            r->p->one_block_kernel = true;  // geometries that the table launches carry
+            r->p->one_block_kernel = true;  // geometries that the service launches carry
             if (phia_anneal_start(r->p, r->R, r->max_steps, &r->sched, r->seed) != PHIA_OK)
                 r->failed = true;
             else
