@@ -91,7 +91,9 @@ WORKLOADS = {
 CSRC = os.path.join(ROOT, "paper_2407_10205_amd", "csrc")
 # sources whose hash identifies each profiled kernel's code
 KERNEL_SRCS = {"k_batch_fp4": ["phia_batch_kernel.hip", "phia_devsweep.h", "phia_devmath.h"],
-               "k_sweep_valu": ["phia_valu_kernel.hip", "phia_devsweep.h", "phia_devmath.h"]}
+               "k_sweep_valu": ["phia_valu_kernel.hip", "phia_devsweep.h", "phia_devmath.h"],
+               "k_sweep_res": ["phia_resident_kernel.hip", "phia_devsweep.h", "phia_devmath.h"],
+               "k_sweep_split": ["phia_split_kernel.hip", "phia_devsweep.h", "phia_devmath.h"]}
 DEFAULT_SRCS = ["phia_kernels.hip", "phia_devsweep.h", "phia_devmath.h"]
 PROFILES = os.path.join(ROOT, "profiles")
 COPY_BYTES = 256 << 20  # plain device copy used to calibrate the byte counters
@@ -718,12 +720,18 @@ def main():
     Np = info["Np"]
     mfma_ops = 2.0 * Np * Np * (math.ceil(R / info["rows_per_block"]) * info["rows_per_block"]) * T
     fp4_ops = info["sweep_kernel"] == 2  # interleaved sweep with FP4 MFMA operands
+    if info["sweep_kernel"] == 5:  # resident sweep: FP4 operands where every coupling is a code
+        fp4_ops = bool(np.isin(np.abs(np.rint(J * 2.0 ** info["frac_bits"])), (0, 1, 2, 3, 4, 6)).all())
     if fp4_ops:
         Nk = math.ceil(Np / 128) * 128  # FP4 products run over 128-wide k blocks
         mfma_ops = 2.0 * Nk * Np * (math.ceil(R / info["rows_per_block"]) * info["rows_per_block"]) * T
+    if info["sweep_kernel"] in (5, 6):  # 16-row products for 4 or 16 replicas, one per int8 plane
+        mfma_ops *= 16 / info["rows_per_block"]
+    if info["sweep_kernel"] == 6:
+        mfma_ops *= {"i8": 1, "bf16hilo": 2, "fp32": 3}.get(info["path_name"], 0)
     if inc_stats is not None:
         mfma_ops *= inc_stats["kblocks_frac"]
-    mfma_peak = (FP4_MFMA_PEAK if fp4_ops else INT8_MFMA_PEAK if info["path_name"] == "i8"
+    mfma_peak = (FP4_MFMA_PEAK if fp4_ops else INT8_MFMA_PEAK if info["path_name"] == "i8" or info["sweep_kernel"] == 6
                  else BF16_MFMA_PEAK * 0.5)
     geometry = {k: info[k] for k in ("group", "rows_per_block", "j_in_lds", "sweep_kernel", "group_on_one_xcd",
                                      "incremental")}
@@ -731,8 +739,8 @@ def main():
     profile_key = (args.workload + (f"_{args.path}" if args.path != w.get("path", "i8") else "") +
                    ("_poly2" if args.deriv == "poly2" else "") + ("_mh" if mh is not None else "") +
                    ("_full" if args.no_incremental else "") + (f"_r{R}" if args.replicas else ""))
-    kernel = ("k_sweep_valu" if info["sweep_kernel"] == 4 else
-              "k_sweep_pp" if info["sweep_kernel"] >= 1 else "k_sweep_mfma")
+    kernel = {0: "k_sweep_mfma", 4: "k_sweep_valu", 5: "k_sweep_res", 6: "k_sweep_split"}.get(info["sweep_kernel"],
+                                                                                             "k_sweep_pp")
     if info["sweep_kernel"] == 4:
         mfma_ops = 0.0  # J.s on the vector ALUs
     if args.geometry_out:
@@ -800,7 +808,7 @@ def main():
         "metric": "spin-updates/s", "value": value, "unit": "spin-updates/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_step, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None,
-        "dtype": "fp4 (int8 couplings held exactly as E2M1)" if info["sweep_kernel"] == 2 else info["path_name"],
+        "dtype": "fp4 (int8 couplings held exactly as E2M1)" if fp4_ops else info["path_name"],
         "data": "synthetic",
         "config": {"workload": w["desc"], "N": N, "replicas": R, "hmc_steps": T, "path": info["path_name"],
                    "schedule": dict(s, deriv=args.deriv, **({} if mh is None else {"mh_up": mh[0], "mh_down": mh[1]})),
