@@ -735,7 +735,7 @@ static void choose_geometry(phia_problem* p, int R)
     // replicas): FP32 N = 32 3.4 / 1.3-1.5, N = 500 32-69 / 1.4-4.2; BF16
     // hi/lo N = 200 4.2-4.5 / 1.3-1.9, N = 1000 5.7-19 / 1.5-9.6; int8
     // N = 513 2.8-7.9 / 1.3-6.4, N = 900 2.6-11.9 / 1.3-8.9, N = 2000
-    // 5.2-17.5 / 1.6-12.3.  BF16 hi/lo up to 128 columns keeps one workgroup
+    // 5.2-17.5 / 1.6-11.6.  BF16 hi/lo up to 128 columns keeps one workgroup
     // per block, which needs no exchange (N = 64 1.25 / 1.29 at 16 replicas,
     // 1.36 / 2.9 at 4096).
     if (p->Np > (p->path == PHIA_PATH_BF16HILO ? 128 : 512) && make_geometry_split(p, R, 0, 0, p->geo)) return;

@@ -42,9 +42,9 @@
 // What bounds it: the chain of a step (publish, L2, poll, unpack, barrier,
 // products, kick), 1.3 us at four replicas and 1.5 us at sixteen, and per k
 // block and plane the products (N = 2000, four replicas, 1.6 us; sixteen,
-// 2.9 us).  us per step, the sweeps it took the place of / this: N = 500 FP32,
+// 2.7 us).  us per step, the sweeps it took the place of / this: N = 500 FP32,
 // 128 replicas 31.7 / 1.50; N = 1000 BF16 hi/lo, 128 replicas 12.1 / 1.95;
-// N = 2000 int8, 16 replicas 5.2 / 1.63, 512 replicas 8.6 / 6.2; 3-regular
+// N = 2000 int8, 16 replicas 5.2 / 1.63, 512 replicas 8.6 / 5.6; 3-regular
 // N = 4000, 32 replicas 3.5 / 1.55, 64 replicas 3.54 / 2.05.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -66,6 +66,14 @@ __host__ __device__ inline uint32_t split_srow(int nkb) { return 64u * static_ca
 
 constexpr int kSplitDepth = 4;  // spin fragments in flight
 constexpr int kSplitSlots = 4;  // ELL slots of a column in VGPRs
+
+// Sixteen replicas, eight waves and 25 or more k blocks: two waves share the
+// products of their two column blocks, half of the k blocks each, and hand each
+// other a half product through LDS.  It halves the LDS reads of the spins, at
+// N = 2000 2000 cycles of a step, for one more barrier (us per step without /
+// with it: N = 2000, 512 replicas in two passes, 5.98 / 5.61; but 24 k blocks,
+// N = 1500, 2.53 / 2.58, 16 2.0 / 2.1, four waves 3.16 / 3.26).
+__host__ __device__ constexpr bool split_pair(int nkb, int waves, bool few) { return !few && waves == 8 && nkb > 24; }
 
 __device__ __forceinline__ v4i pack16(const int (&c)[16])
 {
@@ -157,6 +165,8 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW
     constexpr int TPR = 64 * NW / RB;  // gathering threads per replica row
     constexpr int NU = (4 * NKB + TPR - 1) / TPR;
     constexpr uint32_t srow = 64u * NKB + 16u, sbuf = RB * srow;
+    constexpr bool PAIR = split_pair(NKB, NW, FEW);
+    constexpr int KH = PAIR ? NKB / 2 : NKB;  // k blocks per wave and column block
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -185,13 +195,19 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW
     constexpr int PN = PL > 0 ? PL : 1, KN = PL > 0 ? NKB : 1;
     v4i jr[KN][PN];
     int32_t slot[kSplitSlots];  // ELL: (coupling << 16) | column
+    v4i* const sP = reinterpret_cast<v4i*>(sS + 2u * sbuf);  // PAIR: [waves][64] half products
     int32_t* const sL = reinterpret_cast<int32_t*>(sS + 2u * sbuf);  // ELL: [slots][16 NW]
     if constexpr (PL > 0) {
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
             for (int pl = 0; pl < PL; ++pl) jr[kb][pl] = v4i{0, 0, 0, 0};
-            if (cval && kb < nkb) load_planes<PN>(a.J, Np, cblk, kb, lane, jr[kb]);
+            if constexpr (PAIR) {
+                const int cb = cb0 + (wave & ~1) + kb / KH, k = (wave & 1) * KH + kb % KH;
+                if (cb < cb1 && k < nkb) load_planes<PN>(a.J, Np, cb, k, lane, jr[kb]);
+            } else {
+                if (cval && kb < nkb) load_planes<PN>(a.J, Np, cblk, kb, lane, jr[kb]);
+            }
         }
     } else {
         const int32_t* E = static_cast<const int32_t*>(a.J);
@@ -340,9 +356,8 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW
                     if (lane < RB) sE[r3n * 16 + lane] = 0;
                 }
                 leave = abort_flag != 0;
-                if (!closing && cval) {
-                    float If[E];
-                    int field[E];  // J s
+                int field[E];  // J s
+                if (!closing && (PAIR ? cb0 + (wave & ~1) < cb1 : cval)) {
                     if constexpr (PL == 0) {
                         static_assert(PL > 0 || FEW, "ELL: four replicas per group");
                         const int8_t* const Sg = reinterpret_cast<const int8_t*>(S + static_cast<uint32_t>(lg) * srow);
@@ -360,35 +375,56 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW
                         // A ring of spin fragments keeps the LDS reads ahead of
                         // the products (the compiler reads two at a time and
                         // waits for them).
-                        constexpr int D = NKB < kSplitDepth ? NKB : kSplitDepth;
-                        v4i acc[PN];
+                        constexpr int D = KH < kSplitDepth ? KH : kSplitDepth, NB = PAIR ? 2 : 1;
+                        v4i acc[NB][PN];
 #pragma unroll
-                        for (int pl = 0; pl < PL; ++pl) acc[pl] = v4i{0, 0, 0, 0};
-                        const unsigned char* const Sr = S + static_cast<uint32_t>(FEW ? lr >> 2 : lr) * srow + 16 * lg;
+                        for (int b = 0; b < NB; ++b)
+#pragma unroll
+                            for (int pl = 0; pl < PL; ++pl) acc[b][pl] = v4i{0, 0, 0, 0};
+                        const unsigned char* const Sr = S + static_cast<uint32_t>(FEW ? lr >> 2 : lr) * srow + 16 * lg +
+                                                        (PAIR ? (wave & 1) * KH * 64 : 0);
                         v4i ring[D];
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (int kb = 0; kb < D; ++kb) ring[kb] = *reinterpret_cast<const v4i*>(Sr + kb * 64);
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int kb = 0; kb < NKB; ++kb) {
+                        for (int kb = 0; kb < KH; ++kb) {
                             const v4i s4 = ring[kb % D];
 #pragma unroll
-                            for (int pl = 0; pl < PL; ++pl)
-                                acc[pl] = FEW ? __builtin_amdgcn_mfma_i32_16x16x64_i8(s4, jr[kb][pl], acc[pl], 0, 0, 0)
-                                              : __builtin_amdgcn_mfma_i32_16x16x64_i8(jr[kb][pl], s4, acc[pl], 0, 0, 0);
-                            if (kb + D < NKB) {
+                            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                                for (int pl = 0; pl < PL; ++pl) {
+                                    const v4i j4 = jr[b * KH + kb][pl];
+                                    acc[b][pl] = FEW ? __builtin_amdgcn_mfma_i32_16x16x64_i8(s4, j4, acc[b][pl], 0, 0, 0)
+                                                     : __builtin_amdgcn_mfma_i32_16x16x64_i8(j4, s4, acc[b][pl], 0, 0, 0);
+                                }
+                            if (kb + D < KH) {
                                 ring[kb % D] = *reinterpret_cast<const v4i*>(Sr + (kb + D) * 64);
                                 __builtin_amdgcn_sched_barrier(0);
                             }
                         }
 #pragma unroll
-                        for (int e = 0; e < E; ++e) {
-                            field[e] = acc[PN - 1][e];
+                        for (int b = 0; b < NB; ++b)
 #pragma unroll
-                            for (int pl = PL - 2; pl >= 0; --pl) field[e] = (field[e] << 8) + acc[pl][e];
-                        }
+                            for (int pl = PL - 2; pl >= 0; --pl)
+#pragma unroll
+                                for (int e = 0; e < E; ++e)
+                                    acc[b][pl][e] += acc[b][pl + 1][e] << 8;
+                        const bool upper = PAIR && (wave & 1);
+#pragma unroll
+                        for (int e = 0; e < E; ++e) field[e] = upper ? acc[NB - 1][0][e] : acc[0][0][e];
+                        if constexpr (PAIR) sP[wave * 64 + lane] = upper ? acc[0][0] : acc[1][0];
                     }
+                }
+                if (PAIR && !closing) __syncthreads();  // the partners' halves
+                if (!closing && cval) {
+                    if constexpr (PAIR) {
+                        const v4i half = sP[(wave ^ 1) * 64 + lane];
+#pragma unroll
+                        for (int e = 0; e < E; ++e) field[e] += half[e];
+                    }
+                    float If[E];
                     int q = 0;
 #pragma unroll
                     for (int e = 0; e < E; ++e) {
@@ -518,6 +554,7 @@ const SplitVariant* split_variant(int Np, int planes)
 size_t split_lds(const SplitVariant& v, int rows, int slots)
 {
     return kSplitSpins + 2u * static_cast<size_t>(rows) * split_srow(v.nkb) +
+           (v.planes > 0 && split_pair(v.nkb, v.waves, rows == 4) ? 1024u * static_cast<size_t>(v.waves) : 0u) +
            (v.planes == 0 ? 64u * static_cast<size_t>(v.waves) * std::max(0, slots - kSplitSlots) : 0u);
 }
 
