@@ -292,15 +292,17 @@ phia_status phia_incremental_stats(phia_problem* p, int64_t* out);
  * spins every step through tagged words; the tag is a sequence number that
  * runs on across launches and restarts (with the words cleared) before it
  * would wrap: 24 bits in the interleaved sweep (sweep_kernel 1), 32 bits in
- * the one-block-per-workgroup sweep.
+ * the one-block-per-workgroup sweep.  In the split sweep (6) the tag is the
+ * low 16 bits of a number that only ever runs on.
  *
  * phia_set_exchange_seq sets the sequence number of the next launch of the
  * current anneal, so that a test can start next to the wrap.  seq must not
- * exceed 2^24 - 2 (interleaved) or 2^32 - 2.  PHIA_ESTATE before
+ * exceed 2^24 - 2 (interleaved), 65520 (split) or 2^32 - 2.  PHIA_ESTATE before
  * phia_anneal_start or when the geometry has no exchange (group 1);
  * PHIA_EINVAL when seq is out of range.
  *
- * A kernel polls one exchange word at most 2^21 times before it gives up;
+ * A kernel polls one exchange word at most 2^21 times before it gives up (the
+ * split sweep polls the first word of a launch for up to a minute);
  * every 256th poll it also gives up if the device error word is raised.  A
  * wait that gives up raises the word, every workgroup leaves the sweep at
  * its next check, and phia_sync then returns PHIA_EDEVICE and poisons the
