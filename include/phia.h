@@ -215,7 +215,10 @@ phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps,
                               const phia_schedule* schedule, uint64_t seed);
 
 /* Enqueue steps [current, k_end) (k_end <= steps).  Returns without waiting;
- * splitting a run into several calls gives bit-identical results. */
+ * splitting a run into several calls gives bit-identical results.  May be
+ * recorded by a stream capture on the problem's stream (phia_anneal_start
+ * synchronises and may not): every replay of the graph runs the same steps on
+ * the state that it finds, any number of times. */
 phia_status phia_anneal_run(phia_problem* p, int64_t k_end);
 
 /* Wait for the problem's stream and report a device error or barrier timeout. */

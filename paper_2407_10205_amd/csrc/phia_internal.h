@@ -112,6 +112,9 @@ size_t sweep_mfma_lds_bytes(int path, int mt, const SweepArgs& a);
 // out: (energy, replica, *err or 0), then with bestS the winner's n spins at byte 64
 hipError_t launch_argmin(const int64_t* bestE, int32_t R, int64_t* out, hipStream_t st,
                          const int8_t* bestS = nullptr, int32_t Np = 0, int32_t n = 0, const int32_t* err = nullptr);
+// Set the 64-bit words of `bytes` bytes of device memory to v by a kernel: a
+// stream capture records an ordinary launch, not a memset node.
+hipError_t fill_words(void* p, uint64_t v, size_t bytes, hipStream_t st);
 // n problems' argmins in one launch (phia_server_kernels.hip): pairs[2 j], pairs[2 j + 1] =
 // (energy, replica) of problem j, errs[j] = *err[j] (0 for a null err[j]).
 hipError_t launch_argmin_many(const int64_t* const* bestE, const int32_t* R, const int32_t* const* err, int n,

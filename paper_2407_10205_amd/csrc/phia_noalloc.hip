@@ -49,28 +49,29 @@ hipError_t scratch_address(int dev, unsigned char** out)
     return hipSuccess;
 }
 
-// Zero n 64-bit words (a kernel, so the clearing is an ordinary launch).
-__global__ void __launch_bounds__(256) k_zero_words(uint64_t* p, size_t n)
+// Set n 64-bit words (a kernel, so the clearing is an ordinary launch).
+__global__ void __launch_bounds__(256) k_fill_words(uint64_t* p, uint64_t v, size_t n)
 {
     for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
          i += static_cast<size_t>(gridDim.x) * blockDim.x)
-        p[i] = 0;
-}
-
-hipError_t zero_words(void* p, size_t bytes, hipStream_t st)
-{
-    const size_t n = bytes / 8;
-    if (n == 0) return hipSuccess;
-    size_t blocks = (n + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_zero_words, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
-                       static_cast<uint64_t*>(p), n);
-    return hipGetLastError();
+        p[i] = v;
 }
 
 size_t round256(size_t b) { return (b + 255) & ~static_cast<size_t>(255); }
 
 }  // namespace
+
+hipError_t fill_words(void* p, uint64_t v, size_t bytes, hipStream_t st)
+{
+    const size_t n = bytes / 8;
+    if (n == 0) return hipSuccess;
+    size_t blocks = (n + 255) / 256;
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(k_fill_words, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
+                       static_cast<uint64_t*>(p), v, n);
+    return hipGetLastError();
+}
+
 }  // namespace phia
 
 using namespace phia;
@@ -136,9 +137,9 @@ extern "C" phia_status phia_anneal_noalloc(phia_problem* p, int32_t replicas, in
     const hipStream_t stream = p->st;
     // the synchronous copy completes before the host table goes out of scope
     if ((e = hipMemcpy(dctab, ctab.data(), sizeof(float) * ctab.size(), hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = zero_words(derr, 256, stream)) != hipSuccess ||
-        (group && (e = zero_words(base + xb_off, xb, stream)) != hipSuccess) ||
-        (pb && (e = zero_words(base + pb_off, pb, stream)) != hipSuccess))
+        (e = fill_words(derr, 0, 256, stream)) != hipSuccess ||
+        (group && (e = fill_words(base + xb_off, 0, xb, stream)) != hipSuccess) ||
+        (pb && (e = fill_words(base + pb_off, 0, pb, stream)) != hipSuccess))
         return hip_fail(p, e, "scratch set-up");
 
     SweepArgs a = sweep_args(p);

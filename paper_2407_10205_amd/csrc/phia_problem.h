@@ -124,7 +124,9 @@ struct phia_problem {
     int64_t* detrace = nullptr;
     uint64_t* dxbits = nullptr;
     uint64_t* dpbuf = nullptr;
+    size_t xb_bytes = 0, pb_bytes = 0, mb_bytes = 0;  // of dxbits, dpbuf, dmhbuf
     uint32_t seq = 0;
+    bool recorded = false;  // a stream capture holds a sweep of this state with an exchange
     bool err_live = false;  // launches since the last phia_sync may have raised the error word
     bool give_up = false;  // test hook: the device error word is raised before every sweep launch
     int32_t best_r = -1;

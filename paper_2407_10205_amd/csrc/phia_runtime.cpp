@@ -791,6 +791,8 @@ void free_state(phia_problem* p)
     dfree(p->dmhc);
     dfree(p->dmhbuf);
     p->mhQ_cap = 0;
+    p->xb_bytes = p->pb_bytes = p->mb_bytes = 0;
+    p->recorded = false;
     p->state_bytes = 0;
     p->R = 0;
     p->T = 0;
@@ -1208,6 +1210,7 @@ phia_status setup_mh_geometry(phia_problem* p)
         const size_t mb = 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.G * p->geo.rows * 4 * sizeof(uint64_t);
         if ((e = dalloc(reinterpret_cast<void**>(&p->dmhbuf), mb, cnt)) != hipSuccess)
             return fail(PHIA_ENOMEM, "accept/reject exchange allocation failed");
+        p->mb_bytes = mb;
         if ((e = hipMemsetAsync(p->dmhbuf, 0, mb, p->st)) != hipSuccess) return hip_fail(p, e, "exchange reset");
     }
     return PHIA_OK;
@@ -1340,6 +1343,8 @@ phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps, 
             free_state(p);
             return fail(PHIA_ENOMEM, "exchange buffer allocation failed");
         }
+        p->xb_bytes = xb;
+        p->pb_bytes = pb;
         if ((e = hipMemsetAsync(p->dxbits, 0, xb, p->st)) != hipSuccess ||
             (pb && (e = hipMemsetAsync(p->dpbuf, 0, pb, p->st)) != hipSuccess))
             return hip_fail(p, e, "exchange buffer reset");
@@ -1359,20 +1364,13 @@ phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps, 
 
 namespace phia {
 
-// Zero the exchange words of the current geometry (their tags restart at 1).
+// Zero the exchange words (their tags restart at 1).
 hipError_t clear_exchange(phia_problem* p)
 {
     hipError_t e = hipSuccess;
-    const size_t xb = 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.rows * (p->Np / 16) * sizeof(uint64_t);
-    if (p->dxbits) e = hipMemsetAsync(p->dxbits, 0, xb, p->st);
-    if (e == hipSuccess && p->dpbuf) {
-        const size_t pb = 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.G * p->geo.rows * 2 * sizeof(uint64_t);
-        e = hipMemsetAsync(p->dpbuf, 0, pb, p->st);
-    }
-    if (e == hipSuccess && p->dmhbuf) {
-        const size_t mb = 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.G * p->geo.rows * 4 * sizeof(uint64_t);
-        e = hipMemsetAsync(p->dmhbuf, 0, mb, p->st);
-    }
+    if (p->dxbits) e = fill_words(p->dxbits, 0, p->xb_bytes, p->st);
+    if (e == hipSuccess && p->dpbuf) e = fill_words(p->dpbuf, 0, p->pb_bytes, p->st);
+    if (e == hipSuccess && p->dmhbuf) e = fill_words(p->dmhbuf, 0, p->mb_bytes, p->st);
     return e;
 }
 
@@ -1391,30 +1389,41 @@ phia_status phia_anneal_run(phia_problem* p, int64_t k_end)
     if (k_end == p->k) return PHIA_OK;
     hipError_t e = hipSetDevice(p->dev);
     if (e != hipSuccess) return hip_fail(p, e, "hipSetDevice");
-    if (p->geo.kind == 6 && p->st && !p->give_up) {
-        // Under stream capture the launches are recorded, and a replay would
-        // meet the tags of the launch before it: where there is a sweep
-        // without an exchange for this shape, that one is recorded.
+    if (p->geo.G > 1 && p->st) {
+        // A replay of a recorded launch meets the words of whatever ran before
+        // it, their tags among them: a whole anneal earlier, possibly the very
+        // ones it waits for (the split sweep's repeat after 2^16 steps, and
+        // every sweep's after one).  So the recorded launch starts from cleared
+        // words, and so does every later one on this state, as replays may come
+        // in between.  Where the split sweep's shape has a sweep without an
+        // exchange, that one is recorded.
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(p->st, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive) {
-            const Geometry split = p->geo;
-            p->no_split = true;
-            choose_geometry(p, p->R);
-            p->no_split = false;
-            if (p->geo.ok && p->geo.G == 1) {
-                st = phia_anneal_run(p, k_end);
+            if (p->geo.kind == 6 && !p->give_up) {
+                const Geometry split = p->geo;
+                p->no_split = true;
+                choose_geometry(p, p->R);
+                p->no_split = false;
+                if (p->geo.ok && p->geo.G == 1) {
+                    st = phia_anneal_run(p, k_end);
+                    p->geo = split;
+                    return st;
+                }
                 p->geo = split;
-                return st;
             }
-            p->geo = split;
+            p->recorded = true;
         }
+    }
+    if (p->recorded && p->geo.G > 1) {
+        if ((e = clear_exchange(p)) != hipSuccess) return hip_fail(p, e, "exchange reset");
+        p->seq = 0;
     }
     SweepArgs a = sweep_args(p);
     a.k0 = p->k;
     a.k1 = k_end;
     // test hook: the error word raised before the launch, as if another
     // workgroup had given up
-    if (p->give_up && (e = hipMemsetAsync(p->derr, 0x02, 1, p->st)) != hipSuccess)
+    if (p->give_up && (e = fill_words(p->derr, 2, 8, p->st)) != hipSuccess)
         return hip_fail(p, e, "error word");
     if (p->give_up || p->geo.G > 1) p->err_live = true;
     if (p->geo.kind == 5) {
