@@ -1504,8 +1504,8 @@ phia_status phia_sync(phia_problem* p)
     hipError_t e = hipSetDevice(p->dev);
     if (e == hipSuccess) e = p->st ? hipStreamSynchronize(p->st) : hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(p, e, "synchronise");
-    // only launches with an exchange between workgroups raise the error word
-    if (!p->err_live) return PHIA_OK;
+    // only launches with an exchange between workgroups raise the error word (recorded ones at any time)
+    if (!p->err_live && !p->recorded) return PHIA_OK;
     int32_t err = 0;
     e = hipMemcpy(&err, p->derr, sizeof err, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(p, e, "read device error word");
@@ -1578,7 +1578,7 @@ static phia_status read_best(phia_problem* p, int64_t* res, int8_t* spins)
     const int n = spins ? p->N : 0;
     alignas(8) unsigned char buf[64 + 16384];  // N <= 16384
     hipError_t e = launch_argmin(p->dbestE, p->R, p->dscratch, p->st, spins ? p->dbestS : nullptr, p->Np, n,
-                                 p->err_live ? p->derr : nullptr);
+                                 p->err_live || p->recorded ? p->derr : nullptr);
     if (e != hipSuccess) return hip_fail(p, e, "argmin launch");
     if ((e = hipMemcpyAsync(buf, p->dscratch, n ? 64 + static_cast<size_t>(n) : 24, hipMemcpyDeviceToHost, p->st)) !=
             hipSuccess ||

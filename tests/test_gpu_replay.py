@@ -59,3 +59,28 @@ def test_replays_equal_eager_runs(monkeypatch, spec, path, N, R, n):
             for a, b in zip(ref[i], state(p)):
                 assert np.array_equal(a, b), i
             torch.randn(512, 512, device="cuda").matmul(torch.randn(512, 512, device="cuda")).sum().item()
+
+
+def test_error_word_of_a_replay_is_reported(monkeypatch):
+    """A wait that gives up in a replay (the error word raised from the host's
+    hook, recorded with the sweep) is reported by the next synchronisation,
+    also when an earlier one has found the word clear."""
+    import torch
+    from paper_2407_10205_amd import phia as P
+    J, h = inst.sk_gauss_fixed(600, 3, frac_bits=5, bits=8)
+    monkeypatch.setenv("PHIA_GEOMETRY", "split,16")
+    st = torch.cuda.Stream()
+    with P.Problem(J, h, frac_bits=5, path="i8", stream=st.cuda_stream) as p:
+        p.start(20, 30, eps=0.2, gamma=1.0, beta0=0.01, beta1=0.3, refresh_L=9, seed=2)
+        p.run(5)
+        p.sync()
+        p.raise_error_word()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            p.run(30)
+        p.sync()
+        g.replay()
+        torch.cuda.synchronize()
+        with pytest.raises(P.PhiaError) as e:
+            p.best()
+        assert e.value.code == -6
