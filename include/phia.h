@@ -210,6 +210,15 @@ int32_t phia_valu_crossover(int32_t Np);
  * couplings that one CU holds run the resident sweep (sweep_kernel 5); larger
  * ones, FP32, 16-bit and sparse couplings the split sweep (6); the accept/reject step,
  * energy traces and Np > 2048 the other sweeps.
+ * The split sweep and the other sweeps whose workgroups exchange spins are
+ * cooperative launches: they run one after the other, whatever their streams,
+ * and one may fill the device.  On a stream of its own an anneal therefore
+ * keeps the sweep without an exchange where several of them side by side
+ * finish sooner (sparse couplings; 16-bit ones up to 192 columns and FP32 ones
+ * up to 48, with up to 1024 replicas).  Their waits for each other are bounded
+ * (see phia_set_exchange_seq): a split launch whose workgroups cannot all start
+ * because another stream's kernels hold the device for more than a minute
+ * ends in PHIA_EDEVICE, so keep kernels that run beside it shorter than that.
  * A tuned or cached geometry (phia_autotune) takes precedence. */
 phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps,
                               const phia_schedule* schedule, uint64_t seed);

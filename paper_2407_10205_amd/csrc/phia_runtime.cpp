@@ -652,6 +652,25 @@ static bool resident_wins(const phia_problem* p, int R)
     return R <= (p->Np <= 128 ? 4096 : 3072);
 }
 
+// Anneals on streams of their own run side by side, exchange sweeps do not: the
+// runtime runs cooperative launches one after the other, and a group of four
+// replicas spreads over as many CUs as it can use.  So on a stream of its own
+// an anneal keeps the sweep without an exchange where four of them side by
+// side (the process's hardware queues) finish more per second; on the null
+// stream nothing runs beside it.  us per step and anneal on 1, 2 and 4 streams,
+// without exchange / split: 3-regular N = 1000, 64 replicas 1.56 0.78 0.39 /
+// 1.26 1.26 1.25, N = 4000 3.6 1.8 1.1 / 2.0 1.9 1.9; BF16 hi/lo N = 130, 16
+// replicas 2.57 1.28 0.65 / 1.14 1.14 1.13, but N = 256 4.24 2.12 1.07 / 1.16
+// 1.15 1.14; FP32 N = 16 2.67 1.36 0.68 / 1.19 1.18 1.17, but N = 64 4.75 2.38
+// 1.2 / 1.18 1.18 1.18.  Beyond 1024 replicas one anneal takes a quarter of
+// the device and more.  (phia_autotune picks what is fastest alone.)
+static bool runs_beside_others(const phia_problem* p, int R)
+{
+    if (!p->st || p->one_block_kernel) return false;
+    if (p->path == PHIA_PATH_ELL) return true;
+    return R <= 1024 && (p->path == PHIA_PATH_BF16HILO ? p->Np <= 192 : p->path == PHIA_PATH_FP32 && p->N <= 48);
+}
+
 static void choose_geometry(phia_problem* p, int R)
 {
     p->geo.ok = false;
@@ -719,7 +738,7 @@ static void choose_geometry(phia_problem* p, int R)
         // rows, us per step, VALU / split: N = 1000 1.55 / 1.36 at 64 replicas,
         // 1.61 / 1.95 at 256; N = 2000 2.0 / 1.4-2.0 up to 128; N = 4000 3.5 /
         // 1.5 at 32, 3.5 / 2.05 at 64; two passes, 128 replicas, 3.7 / 4.2).
-        if (make_geometry_split(p, R, 0, 0, p->geo)) {
+        if (!runs_beside_others(p, R) && make_geometry_split(p, R, 0, 0, p->geo)) {
             if (p->path == PHIA_PATH_FP32 || p->Np > 1024 || (p->Np > 512 && p->Np / 16 <= 8 * p->geo.G)) return;
             p->geo = Geometry{};
         }
@@ -738,7 +757,9 @@ static void choose_geometry(phia_problem* p, int R)
     // 5.2-17.5 / 1.6-11.6.  BF16 hi/lo up to 128 columns keeps one workgroup
     // per block, which needs no exchange (N = 64 1.25 / 1.29 at 16 replicas,
     // 1.36 / 2.9 at 4096).
-    if (p->Np > (p->path == PHIA_PATH_BF16HILO ? 128 : 512) && make_geometry_split(p, R, 0, 0, p->geo)) return;
+    if (p->Np > (p->path == PHIA_PATH_BF16HILO ? 128 : 512) && !runs_beside_others(p, R) &&
+        make_geometry_split(p, R, 0, 0, p->geo))
+        return;
     // Few replicas on the int8 path: the VALU dot-product sweep.
     if (p->path == PHIA_PATH_I8 && R <= valu_fallback(p->Np) && make_geometry_valu(p, R, valu_rows(R), p->geo))
         return;

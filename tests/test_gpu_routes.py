@@ -1,0 +1,41 @@
+"""Which sweep an anneal takes by default, beside the rules that the tests of
+the single sweeps check: streams, replica counts, settings and files that
+have a say in it, on both sides of each line."""
+import numpy as np
+import pytest
+
+from paper_2407_10205_amd import instances as inst
+
+pytestmark = pytest.mark.gpu
+
+SCHED = dict(eps=0.2, gamma=1.0, beta0=0.01, beta1=0.02, refresh_L=25)
+
+
+def couplings(path, N):
+    """Couplings that the path holds and no narrower one does."""
+    if path == "ell":
+        return inst.regular3_pm1(N, 1)
+    f, bits = {"i8": (5, 8), "bf16hilo": (9, 16), "fp32": (12, 20)}[path]
+    return inst.sk_gauss_fixed(N, 1, frac_bits=f, bits=bits)
+
+
+def kind(path, N, R, stream=None, setup=None, **kw):
+    from paper_2407_10205_amd import phia as P
+    with P.Problem(*couplings(path, N), path=path, stream=stream) as p:
+        if setup:
+            setup(p)
+        p.anneal(R, 4, **SCHED, **kw)
+        return p.info()["sweep_kernel"]
+
+
+@pytest.mark.parametrize("path,N,R,alone,beside", [
+    ("ell", 1000, 64, 6, 4), ("ell", 4000, 16, 6, 4), ("bf16hilo", 192, 1024, 6, 0), ("bf16hilo", 192, 1025, 6, 6),
+    ("bf16hilo", 193, 16, 6, 6), ("fp32", 48, 1024, 6, 4), ("fp32", 48, 1025, 6, 6), ("fp32", 49, 16, 6, 6),
+    ("i8", 900, 16, 6, 6), ("i8", 300, 16, 5, 5)])
+def test_anneals_on_streams_of_their_own(path, N, R, alone, beside):
+    """On a stream of its own an anneal keeps the sweep without an exchange
+    where several side by side finish sooner by it."""
+    import torch
+    print("stream", path, N, R, flush=True)
+    assert kind(path, N, R) == alone
+    assert kind(path, N, R, stream=torch.cuda.Stream().cuda_stream) == beside
