@@ -754,12 +754,19 @@ static void choose_geometry(phia_problem* p, int R)
     // replicas): FP32 N = 32 3.4 / 1.3-1.5, N = 500 32-69 / 1.4-4.2; BF16
     // hi/lo N = 200 4.2-4.5 / 1.3-1.9, N = 1000 5.7-19 / 1.5-9.6; int8
     // N = 513 2.8-7.9 / 1.3-6.4, N = 900 2.6-11.9 / 1.3-8.9, N = 2000
-    // 5.2-17.5 / 1.6-11.6.  BF16 hi/lo up to 128 columns keeps one workgroup
-    // per block, which needs no exchange (N = 64 1.25 / 1.29 at 16 replicas,
-    // 1.36 / 2.9 at 4096).
+    // 5.2-17.5 / 1.6-11.6.  Further replicas are further passes of both, and
+    // the order stays (FP32 N = 16 44 / 43 at 65536, N = 500 2035 / 137; BF16
+    // hi/lo N = 256 18.6 / 13.2 at 16384; int8 N = 640 67 / 48), except where
+    // one workgroup per block, which needs no exchange, is as quick per pass:
+    // BF16 hi/lo up to 128 columns at every replica count (N = 64 1.25 / 1.29
+    // at 16, 1.36 / 2.9 at 4096) and up to 192 columns past one pass (N = 129
+    // and 192 2.7 / 1.77 at 2048, 2.7-2.8 / 3.3 at 3072, 10.8-11.2 / 12.5 at
+    // 16384).
     if (p->Np > (p->path == PHIA_PATH_BF16HILO ? 128 : 512) && !runs_beside_others(p, R) &&
-        make_geometry_split(p, R, 0, 0, p->geo))
-        return;
+        make_geometry_split(p, R, 0, 0, p->geo)) {
+        if (p->Np > 192 || p->geo.nblocks <= p->geo.ngroups) return;
+        p->geo = Geometry{};
+    }
     // Few replicas on the int8 path: the VALU dot-product sweep.
     if (p->path == PHIA_PATH_I8 && R <= valu_fallback(p->Np) && make_geometry_valu(p, R, valu_rows(R), p->geo))
         return;

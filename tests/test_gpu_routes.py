@@ -39,3 +39,12 @@ def test_anneals_on_streams_of_their_own(path, N, R, alone, beside):
     print("stream", path, N, R, flush=True)
     assert kind(path, N, R) == alone
     assert kind(path, N, R, stream=torch.cuda.Stream().cuda_stream) == beside
+
+
+@pytest.mark.parametrize("path,N,R,want", [
+    ("bf16hilo", 129, 2048, 6), ("bf16hilo", 129, 2049, 0), ("bf16hilo", 192, 4096, 0), ("bf16hilo", 193, 4096, 6),
+    ("fp32", 16, 20000, 6), ("fp32", 200, 4100, 6), ("i8", 640, 2100, 6)])
+def test_split_past_one_pass(path, N, R, want):
+    """More replicas than one pass of the split sweep holds."""
+    print("passes", path, N, R, flush=True)
+    assert kind(path, N, R) == want
