@@ -283,10 +283,12 @@ phia_status phia_get_info(const phia_problem* p, phia_info* out);
  * group of one-row-tile blocks with J streamed from L2, an anneal of its own
  * (not a batch or server launch), and on I8 N <= 4864 (the LDS holds the
  * bookkeeping); phia_info.incremental reports whether the current geometry
- * uses it.  on = 1: wherever it applies.  on = -1 (the default): likewise,
- * except with the accept/reject step, whose rejections return whole replicas
- * to their trajectory start, so that few steps qualify.  on = 0: always the
- * full product.  Takes effect at the next phia_anneal_start or phia_anneal.
+ * uses it.  on = 1: wherever it applies (the default choice of geometry then
+ * takes a sweep that has it before one that does not).  on = -1 (the
+ * default): where the sweep that is chosen anyway has it, except with the
+ * accept/reject step, whose rejections return whole replicas to their
+ * trajectory start, so that few steps qualify.  on = 0: always the full
+ * product.  Takes effect at the next phia_anneal_start or phia_anneal.
  * PHIA_EINVAL if on is not -1, 0 or 1. */
 phia_status phia_set_incremental(phia_problem* p, int32_t on);
 

@@ -625,11 +625,39 @@ static std::vector<Geometry> candidate_geometries(phia_problem* p, int R)
     return out;
 }
 
-// Default geometry without tuning: fewest passes over the replica blocks,
-// then the fewest owned elements per workgroup, then J in LDS.
-// PHIA_GEOMETRY="mt,G,jlds[,cbw[,xcd]]" or "pp,G[,xcd]" / "pp4,G[,xcd]" /
-// "ppg,G[,xcd]" (interleaved, int8 J streamed from global memory), "valu,rb"
-// or "res" forces one candidate (tuning experiments).
+// Default among the one-block and interleaved sweeps, into p->geo: fewest
+// passes over the replica blocks first; among those a geometry without column
+// split, else the interleaved kernel with the smallest group, else the fewest
+// owned elements per workgroup, then J in LDS.
+static void choose_mfma(phia_problem* p, int R)
+{
+    const std::vector<Geometry> cands = candidate_geometries(p, R);
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->dev) != hipSuccess || cus < 1) cus = 256;
+    int min_iters = 1 << 30;
+    for (const Geometry& g : cands)
+        if (g.kind < 4) min_iters = std::min(min_iters, (g.nblocks + g.ngroups - 1) / g.ngroups);
+    double best = 0;
+    for (const Geometry& g : cands) {
+        const int iters = (g.nblocks + g.ngroups - 1) / g.ngroups;
+        if (iters != min_iters || g.kind >= 4) continue;  // those: by the rules above or tuning only
+        const int cbs_max = (p->Np / 16 + g.G - 1) / g.G;
+        const double elems = static_cast<double>(g.rows) * cbs_max * 16;
+        double cost = g.kind >= 1 ? 1e6 + 2 * g.G - (g.kind == 2 ? 1 : 0) + (g.j_lds ? 0 : 0.5)
+                                  : (g.G > 1 ? 2e6 : 0.0) + elems * 2 + (g.j_lds ? 0 : 1);
+        // An interleaved grid that leaves most CUs idle (few replica blocks)
+        // gives way to a larger group: SK N = 2000 with 16 replicas takes
+        // 113 ms at G = 64 against 140 ms at G = 16.
+        if (g.kind >= 1) cost += 1e4 * std::max(0.0, 0.5 - static_cast<double>(g.ngroups) * g.G / cus);
+        // Served requests share cooperative launches: the fewest workgroups.
+        if (p->one_block_kernel) cost = static_cast<double>(g.nblocks) * g.G * 4 + (g.j_lds ? 0 : 1) + g.mt;
+        if (!p->geo.ok || cost < best) {
+            p->geo = g;
+            best = cost;
+        }
+    }
+}
+
 // Replica counts at which the resident sweep is the default where it fits,
 // in us per step, it / the best of the other sweeps:
 //   N = 16    0.40 / 0.95 at 64 replicas, 0.63 / 3.1 at 16384;
@@ -671,6 +699,10 @@ static bool runs_beside_others(const phia_problem* p, int R)
     return R <= 1024 && (p->path == PHIA_PATH_BF16HILO ? p->Np <= 192 : p->path == PHIA_PATH_FP32 && p->N <= 48);
 }
 
+// Launch geometry: forced, tuned, cached, or by the rules below.
+// PHIA_GEOMETRY="mt,G,jlds[,cbw[,xcd]]" or "pp,G[,xcd]" / "pp4,G[,xcd]" /
+// "ppg,G[,xcd]" (interleaved, int8 J streamed from global memory), "valu,rb",
+// "res" or "split[,rows[,G]]" forces one candidate (tuning experiments).
 static void choose_geometry(phia_problem* p, int R)
 {
     p->geo.ok = false;
@@ -747,6 +779,13 @@ static void choose_geometry(phia_problem* p, int R)
     }
     if (p->path == PHIA_PATH_I8 && R <= valu_crossover(p->Np) && make_geometry_valu(p, R, valu_rows(R), p->geo))
         return;
+    // phia_set_incremental(1) asks for the flip-incremental product wherever it
+    // applies: a choice among the sweeps that have it goes before the newer ones.
+    if (p->inc_mode == 1) {
+        choose_mfma(p, R);
+        if (p->geo.ok && p->geo.inc) return;
+        p->geo = Geometry{};
+    }
     // Couplings that one CU holds: the resident sweep (resident_wins).
     if (resident_wins(p, R) && make_geometry_res(p, R, p->geo)) return;
     // The split sweep wherever it applies, int8 only past the sizes of the
@@ -770,34 +809,7 @@ static void choose_geometry(phia_problem* p, int R)
     // Few replicas on the int8 path: the VALU dot-product sweep.
     if (p->path == PHIA_PATH_I8 && R <= valu_fallback(p->Np) && make_geometry_valu(p, R, valu_rows(R), p->geo))
         return;
-    // Fewest passes over the replica blocks first; among those a geometry
-    // without column split, else the interleaved kernel with the smallest
-    // group, else the fewest owned elements per workgroup, then J in LDS.
-    const std::vector<Geometry> cands = candidate_geometries(p, R);
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->dev) != hipSuccess || cus < 1) cus = 256;
-    int min_iters = 1 << 30;
-    for (const Geometry& g : cands)
-        if (g.kind < 4) min_iters = std::min(min_iters, (g.nblocks + g.ngroups - 1) / g.ngroups);
-    double best = 0;
-    for (const Geometry& g : cands) {
-        const int iters = (g.nblocks + g.ngroups - 1) / g.ngroups;
-        if (iters != min_iters || g.kind >= 4) continue;  // those: by the rules above or tuning only
-        const int cbs_max = (p->Np / 16 + g.G - 1) / g.G;
-        const double elems = static_cast<double>(g.rows) * cbs_max * 16;
-        double cost = g.kind >= 1 ? 1e6 + 2 * g.G - (g.kind == 2 ? 1 : 0) + (g.j_lds ? 0 : 0.5)
-                                  : (g.G > 1 ? 2e6 : 0.0) + elems * 2 + (g.j_lds ? 0 : 1);
-        // An interleaved grid that leaves most CUs idle (few replica blocks)
-        // gives way to a larger group: SK N = 2000 with 16 replicas takes
-        // 113 ms at G = 64 against 140 ms at G = 16.
-        if (g.kind >= 1) cost += 1e4 * std::max(0.0, 0.5 - static_cast<double>(g.ngroups) * g.G / cus);
-        // Served requests share cooperative launches: the fewest workgroups.
-        if (p->one_block_kernel) cost = static_cast<double>(g.nblocks) * g.G * 4 + (g.j_lds ? 0 : 1) + g.mt;
-        if (!p->geo.ok || cost < best) {
-            p->geo = g;
-            best = cost;
-        }
-    }
+    choose_mfma(p, R);
 }
 
 void free_state(phia_problem* p)

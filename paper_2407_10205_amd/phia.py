@@ -225,9 +225,9 @@ class Problem:
         _check(lib().phia_set_trace(self._p, 1 if enable else 0))
 
     def set_incremental(self, on=True):
-        """Flip-incremental J.s update where the sweep has it (identical
-        results): True, False, or None for the default (on, except with the
-        accept/reject step)."""
+        """Flip-incremental J.s update (identical results): True for a sweep
+        that has it wherever one applies, False, or None for the default (on
+        where the sweep has it, except with the accept/reject step)."""
         _check(lib().phia_set_incremental(self._p, -1 if on is None else 1 if on else 0))
 
     def incremental_stats(self):

@@ -48,3 +48,23 @@ def test_split_past_one_pass(path, N, R, want):
     """More replicas than one pass of the split sweep holds."""
     print("passes", path, N, R, flush=True)
     assert kind(path, N, R) == want
+
+
+@pytest.mark.parametrize("path,N,R", [("bf16hilo", 1000, 128), ("bf16hilo", 1500, 40)])
+def test_incremental_product_on_request(path, N, R):
+    """phia_set_incremental(1) takes a sweep with the flip-incremental product
+    where there is one; the results are those of the default choice."""
+    from paper_2407_10205_amd import phia as P
+    out = []
+    for on in (None, True):
+        print("incremental", path, N, R, on, flush=True)
+        with P.Problem(*couplings(path, N), path=path) as p:
+            if on:
+                p.set_incremental(True)
+            p.anneal(R, 60, **dict(SCHED, beta1=3.0))
+            i, st = p.info(), p.incremental_stats()
+            assert (i["sweep_kernel"], i["incremental"]) == ((0, 1) if on else (6, 0))
+            assert (st[0] + st[1] > 0) == bool(on)
+            out.append(p.replica_best() + p.get_state()[:2])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
