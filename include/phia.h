@@ -328,17 +328,17 @@ phia_status phia_incremental_stats(phia_problem* p, int64_t* out);
 phia_status phia_set_exchange_seq(phia_problem* p, uint32_t seq);
 phia_status phia_raise_error_word(phia_problem* p, int32_t on);
 
-/* Autotuner of the launch geometry of the matrix-core sweep (replicas per
- * workgroup block, workgroups sharing one block's columns, coupling slice in
- * LDS or streamed): every feasible geometry for `replicas` replicas runs
- * probe_steps steps (in [10, 100000]) on this problem, timed with HIP events
- * on its stream, and the fastest is kept for later anneals with the same
+/* Autotuner of the launch geometry (sweep, replicas per workgroup block,
+ * workgroups sharing one block's columns, coupling slice in LDS or streamed):
+ * every feasible geometry for `replicas` replicas runs probe_steps steps (in
+ * [10, 100000]) on this problem, timed with HIP events on its stream, and the fastest is kept for later anneals with the same
  * replica count.  Ends any anneal in progress (state is released).  When
  * the environment variable PHIA_TUNE_CACHE names a file, the winner is
  * appended to it and problems of the same path, padded size and replica
  * count created later use it without timing.  best_us: host double, time per
- * step of the winner in microseconds, or NULL.  The FP32 path has one
- * geometry and returns at once (best_us = 0). */
+ * step of the winner in microseconds, or NULL.  FP32 and sparse problems
+ * whose last anneal had the accept/reject step have one geometry for it and
+ * return at once (best_us = 0). */
 phia_status phia_autotune(phia_problem* p, int32_t replicas, int64_t probe_steps, double* best_us);
 
 /* Record the energy of every step of the next anneal (test and diagnostic

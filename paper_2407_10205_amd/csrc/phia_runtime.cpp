@@ -579,8 +579,10 @@ static std::vector<Geometry> candidate_geometries(phia_problem* p, int R)
             Geometry g;
             if (make_geometry_valu(p, R, rb, g)) out.push_back(g);
         }
-        Geometry g;
-        if (make_geometry_split(p, R, 4, 0, g)) out.push_back(g);
+        for (const int rows : {4, 16}) {
+            Geometry g;
+            if (make_geometry_split(p, R, rows, 0, g)) out.push_back(g);
+        }
         return out;
     }
     {
@@ -1811,8 +1813,7 @@ phia_status phia_autotune(phia_problem* p, int32_t replicas, int64_t probe_steps
     if (replicas < 1 || replicas > (1 << 20)) return fail(PHIA_EINVAL, "replicas = %d outside [1, 2^20]", replicas);
     if (probe_steps < 10 || probe_steps > 100000) return fail(PHIA_EINVAL, "probe_steps outside [10, 100000]");
     if (best_us) *best_us = 0.0;
-    if (p->path == PHIA_PATH_FP32) return PHIA_OK;  // one launch shape only
-    if (p->path == PHIA_PATH_ELL && p->mh) return PHIA_OK;
+    if ((p->path == PHIA_PATH_FP32 || p->path == PHIA_PATH_ELL) && p->mh) return PHIA_OK;
     std::vector<Geometry> cands = candidate_geometries(p, replicas);
     if (cands.empty()) return fail(PHIA_ERANGE, "no kernel geometry fits N = %d on this device", p->N);
     // Candidates that need more passes over the replica blocks than twice

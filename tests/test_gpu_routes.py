@@ -68,3 +68,22 @@ def test_incremental_product_on_request(path, N, R):
             out.append(p.replica_best() + p.get_state()[:2])
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("path,N,R,kw,want", [
+    ("fp32", 300, 16, {}, 6), ("fp32", 300, 500, {}, 6), ("i8", 300, 64, {}, 5)])
+def test_autotune_times_every_sweep(path, N, R, kw, want):
+    """The autotuner finds the sweep that is fastest by far (FP32: split
+    against VALU), and later anneals take it."""
+    from paper_2407_10205_amd import phia as P
+    print("autotune", path, N, R, kw, flush=True)
+    with P.Problem(*couplings(path, N), path=path) as p:
+        p.anneal(R, 4, **SCHED, **kw)
+        assert p.autotune(R, 100) > 0
+        p.anneal(R, 40, **SCHED)
+        assert p.info()["sweep_kernel"] == want
+        a = p.replica_best()
+    with P.Problem(*couplings(path, N), path=path) as p:
+        p.anneal(R, 40, **SCHED)
+        for x, y in zip(a, p.replica_best()):
+            assert np.array_equal(x, y)
