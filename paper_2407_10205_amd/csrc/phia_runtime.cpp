@@ -1814,6 +1814,7 @@ phia_status phia_autotune(phia_problem* p, int32_t replicas, int64_t probe_steps
     if (probe_steps < 10 || probe_steps > 100000) return fail(PHIA_EINVAL, "probe_steps outside [10, 100000]");
     if (best_us) *best_us = 0.0;
     if ((p->path == PHIA_PATH_FP32 || p->path == PHIA_PATH_ELL) && p->mh) return PHIA_OK;
+    p->ikick = 0;  // the last anneal's, which has candidates of its own; the probes run without
     std::vector<Geometry> cands = candidate_geometries(p, replicas);
     if (cands.empty()) return fail(PHIA_ERANGE, "no kernel geometry fits N = %d on this device", p->N);
     // Candidates that need more passes over the replica blocks than twice

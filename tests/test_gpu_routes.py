@@ -71,10 +71,12 @@ def test_incremental_product_on_request(path, N, R):
 
 
 @pytest.mark.parametrize("path,N,R,kw,want", [
-    ("fp32", 300, 16, {}, 6), ("fp32", 300, 500, {}, 6), ("i8", 300, 64, {}, 5)])
+    ("fp32", 300, 16, {}, 6), ("fp32", 300, 500, {}, 6), ("i8", 300, 64, {}, 5), ("i8", 300, 64, dict(ikick=True), 5),
+    ("i8", 900, 16, dict(ikick=True), 6)])
 def test_autotune_times_every_sweep(path, N, R, kw, want):
     """The autotuner finds the sweep that is fastest by far (FP32: split
-    against VALU), and later anneals take it."""
+    against VALU; also after an anneal with the initial kick, whose only sweep
+    is the VALU one), and later anneals take it."""
     from paper_2407_10205_amd import phia as P
     print("autotune", path, N, R, kw, flush=True)
     with P.Problem(*couplings(path, N), path=path) as p:
