@@ -335,7 +335,8 @@ phia_status phia_raise_error_word(phia_problem* p, int32_t on);
  * replica count.  Ends any anneal in progress (state is released).  When
  * the environment variable PHIA_TUNE_CACHE names a file, the winner is
  * appended to it and problems of the same path, padded size and replica
- * count created later use it without timing.  best_us: host double, time per
+ * count created later use it without timing (lines written before the resident
+ * and split sweeps are skipped where one of these applies).  best_us: host double, time per
  * step of the winner in microseconds, or NULL.  FP32 and sparse problems
  * whose last anneal had the accept/reject step have one geometry for it and
  * return at once (best_us = 0). */

@@ -228,8 +228,11 @@ static void pack_bf16(const std::vector<int32_t>& Ji, int N, int Np, std::vector
 
 // ------------------------------------------------------- kernel geometry --
 // ------------------------------------------------------- tuning cache --
-// One line per tuned shape: "phia-tune4 path Np R kind mt cbw G jlds xcd us_per_step"
+// One line per tuned shape: "phia-tune5 path Np R kind mt cbw G jlds xcd us_per_step"
 // (kinds 4 and 6, the VALU and the split sweep: replicas per workgroup or group in place of mt).
+// Lines with the tag phia-tune4 were timed without the resident and the split
+// sweep and would pin what these take the place of; they count only for
+// shapes that neither holds.
 static const char* tune_cache_path() { return std::getenv("PHIA_TUNE_CACHE"); }
 
 static const char* path_name(int path)
@@ -262,7 +265,9 @@ static bool lookup_tune_cache(phia_problem* p, int R)
     Geometry g;
     while (std::fscanf(f, "%31s %d %d %d %d %d %d %d %d %d %lf", tag, &pa, &np, &r, &kind, &mt, &cbw, &G, &jl, &xcd,
                        &us) == 11) {
-        if (std::strcmp(tag, "phia-tune4") == 0 && pa == p->path && np == p->Np && r == R &&
+        const bool older = std::strcmp(tag, "phia-tune4") == 0;
+        if ((older || std::strcmp(tag, "phia-tune5") == 0) && pa == p->path && np == p->Np && r == R &&
+            !(older && (make_geometry_res(p, R, g) || make_geometry_split(p, R, 0, 0, g))) &&
             (kind == 6   ? make_geometry_split(p, R, mt, G, g)
              : kind == 5 ? make_geometry_res(p, R, g)
              : kind == 4 ? make_geometry_valu(p, R, mt, g)
@@ -282,7 +287,7 @@ static void append_tune_cache(const phia_problem* p, int R, const Geometry& g, d
     if (!path) return;
     FILE* f = std::fopen(path, "a");
     if (!f) return;
-    std::fprintf(f, "phia-tune4 %d %d %d %d %d %d %d %d %d %.3f\n", p->path, p->Np, R, g.kind,
+    std::fprintf(f, "phia-tune5 %d %d %d %d %d %d %d %d %d %.3f\n", p->path, p->Np, R, g.kind,
                  g.kind == 4 || g.kind == 6 ? g.rows : g.mt, g.cbw, g.G,
                  g.j_lds, g.xcd_map, us);
     std::fclose(f);

@@ -89,3 +89,29 @@ def test_autotune_times_every_sweep(path, N, R, kw, want):
         p.anneal(R, 40, **SCHED)
         for x, y in zip(a, p.replica_best()):
             assert np.array_equal(x, y)
+
+
+def test_tune_cache_of_older_sweeps_is_skipped(monkeypatch, tmp_path):
+    """A cache line written before the split sweep does not pin the sweep that
+    it took the place of, but holds where neither it nor the resident sweep
+    applies; one written now is used."""
+    from paper_2407_10205_amd import phia as P
+    f = tmp_path / "tune"
+    monkeypatch.setenv("PHIA_TUNE_CACHE", str(f))
+    Np = 960
+    f.write_text(f"phia-tune4 2 {Np} 16 1 2 1 60 1 0 2.6\n")
+    assert kind("i8", 900, 16) == 6
+    with P.Problem(*couplings("i8", 900), path="i8") as p:
+        assert p.info()["Np"] == Np and p.autotune(16, 50) > 0
+        tuned = p.info()["sweep_kernel"]
+    tag, path, np_, r, k, rows = f.read_text().split("\n")[1].split()[:6]
+    assert (int(path), int(np_), int(r), int(k)) == (2, Np, 16, tuned)
+    f.write_text(f"{tag} 2 {Np} 16 6 16 1 12 1 1 2.0\n")
+    with P.Problem(*couplings("i8", 900), path="i8") as p:
+        p.anneal(16, 4, **SCHED)
+        i = p.info()
+        assert (i["sweep_kernel"], i["rows_per_block"], i["group"]) == (6, 16, 12)
+    f.write_text("phia-tune4 2 2112 16 0 1 2 44 0 0 9.0\n")
+    with P.Problem(*couplings("i8", 2100), path="i8") as p:
+        p.anneal(16, 4, **SCHED)
+        assert (p.info()["sweep_kernel"], p.info()["group"]) == (0, 44)
