@@ -198,6 +198,7 @@ phia_status launch_group_chunk(phia_problem* const* probs, int count, const int6
         offs.push_back(tab.size());
         for (int i : L.members) {
             phia_problem* p = probs[i];
+            if ((e = take_exchange(p, p->geo.kind)) != hipSuccess) return hip_fail(p, e, "exchange reset");
             // 32-bit tags: restart the sequence (cleared words) before it would wrap
             const uint64_t iters = static_cast<uint64_t>((p->geo.nblocks + p->geo.ngroups - 1) / p->geo.ngroups);
             if (static_cast<uint64_t>(p->seq) + iters * static_cast<uint64_t>(k_end[i] - p->k + 1) > 0xfffffffeull) {

@@ -45,6 +45,8 @@ void kick_factors(const ::phia_problem* p, int64_t steps, const phia_schedule* s
 phia_status setup_state(::phia_problem* p, int32_t replicas, int64_t steps, const phia_schedule* s, uint64_t seed,
                         const std::vector<float>& ctab, bool& reuse, bool sync_first);
 void free_state(::phia_problem* p);
+phia_status prepare_table(::phia_problem* p);
+hipError_t take_exchange(::phia_problem* p, int kind);
 hipError_t clear_exchange(::phia_problem* p);
 phia_status make_resident(::phia_problem* p);
 void release_resident(::phia_problem* p);
@@ -132,6 +134,9 @@ struct phia_problem {
     int32_t best_r = -1;
     size_t state_bytes = 0;
     phia::Geometry geo;
+    phia::Geometry table;     // served split sweep: the table launches' geometry (prepare_table)
+    bool table_tried = false;
+    int exchange_kind = 0;    // Geometry::kind of the sweep that wrote the exchange words
     phia::Geometry tuned;  // autotuned geometry for tuned_R replicas
     int32_t tuned_R = 0;
     struct phia_batch* batch = nullptr;  // batch plan that holds the replica state, or null

@@ -819,6 +819,16 @@ static void choose_geometry(phia_problem* p, int R)
     choose_mfma(p, R);
 }
 
+// Bytes of the exchange words and of the partial energies of a geometry.
+static size_t xbits_bytes(const phia_problem* p, const Geometry& g)
+{
+    return 2 * static_cast<size_t>(g.ngroups) * g.rows * (p->Np / 16) * sizeof(uint64_t);
+}
+static size_t pbuf_bytes(const Geometry& g)
+{
+    return 2 * static_cast<size_t>(g.ngroups) * g.G * g.rows * 2 * sizeof(uint64_t);
+}
+
 void free_state(phia_problem* p)
 {
     dfree(p->dx);
@@ -840,6 +850,8 @@ void free_state(phia_problem* p)
     p->mhQ_cap = 0;
     p->xb_bytes = p->pb_bytes = p->mb_bytes = 0;
     p->recorded = false;
+    p->table = Geometry{};
+    p->table_tried = false;
     p->state_bytes = 0;
     p->R = 0;
     p->T = 0;
@@ -1383,8 +1395,7 @@ phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps, 
     if (p->geo.G > 1) {
         // Tagged exchange words start at zero; tags start at 1 (the split
         // sweep's partial energies travel in them).
-        const size_t xb = 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.rows * (p->Np / 16) * sizeof(uint64_t);
-        const size_t pb = p->geo.kind == 6 ? 0 : 2 * static_cast<size_t>(p->geo.ngroups) * p->geo.G * p->geo.rows * 2 * sizeof(uint64_t);
+        const size_t xb = xbits_bytes(p, p->geo), pb = p->geo.kind == 6 ? 0 : pbuf_bytes(p->geo);
         if ((e = dalloc(reinterpret_cast<void**>(&p->dxbits), xb, cnt)) != hipSuccess ||
             (pb && (e = dalloc(reinterpret_cast<void**>(&p->dpbuf), pb, cnt)) != hipSuccess)) {
             free_state(p);
@@ -1396,6 +1407,7 @@ phia_status phia_anneal_start(phia_problem* p, int32_t replicas, int64_t steps, 
             (pb && (e = hipMemsetAsync(p->dpbuf, 0, pb, p->st)) != hipSuccess))
             return hip_fail(p, e, "exchange buffer reset");
         p->seq = 0;
+        p->exchange_kind = p->geo.kind;
     }
     if ((st = setup_mh_geometry(p)) != PHIA_OK) {
         free_state(p);
@@ -1419,6 +1431,46 @@ hipError_t clear_exchange(phia_problem* p)
     if (e == hipSuccess && p->dpbuf) e = fill_words(p->dpbuf, 0, p->pb_bytes, p->st);
     if (e == hipSuccess && p->dmhbuf) e = fill_words(p->dmhbuf, 0, p->mb_bytes, p->st);
     return e;
+}
+
+// A served request on the split sweep that may run in the table launches too:
+// their geometry (p->table, if there is one) and room for their words.  No
+// launch of the request is under way.
+phia_status prepare_table(phia_problem* p)
+{
+    if (p->table_tried) return PHIA_OK;
+    p->table_tried = true;
+    const Geometry own = p->geo;
+    p->geo = Geometry{};
+    choose_mfma(p, p->R);
+    const Geometry g = p->geo;
+    p->geo = own;
+    if (!g.ok || g.kind != 0 || g.G < 2) return PHIA_OK;
+    size_t* cnt = &p->state_bytes;
+    hipError_t e = hipSuccess;
+    if (xbits_bytes(p, g) > p->xb_bytes) {
+        dfree(p->dxbits);
+        p->xb_bytes = xbits_bytes(p, g);
+        e = dalloc(reinterpret_cast<void**>(&p->dxbits), p->xb_bytes, cnt);
+    }
+    if (e == hipSuccess && !p->dpbuf) {
+        p->pb_bytes = pbuf_bytes(g);
+        e = dalloc(reinterpret_cast<void**>(&p->dpbuf), p->pb_bytes, cnt);
+    }
+    if (e != hipSuccess) return fail(PHIA_ENOMEM, "exchange buffer allocation failed");
+    p->exchange_kind = -1;  // cleared by the next launch
+    p->table = g;
+    return PHIA_OK;
+}
+
+// Before a launch of sweep `kind`: the words start over when another sweep
+// wrote them (its tags have another form) or a recorded launch may have.
+hipError_t take_exchange(phia_problem* p, int kind)
+{
+    if (!p->recorded && p->exchange_kind == kind) return hipSuccess;
+    p->seq = 0;
+    p->exchange_kind = kind;
+    return clear_exchange(p);
 }
 
 }  // namespace phia
@@ -1461,10 +1513,7 @@ phia_status phia_anneal_run(phia_problem* p, int64_t k_end)
             p->recorded = true;
         }
     }
-    if (p->recorded && p->geo.G > 1) {
-        if ((e = clear_exchange(p)) != hipSuccess) return hip_fail(p, e, "exchange reset");
-        p->seq = 0;
-    }
+    if (p->geo.G > 1 && (e = take_exchange(p, p->geo.kind)) != hipSuccess) return hip_fail(p, e, "exchange reset");
     SweepArgs a = sweep_args(p);
     a.k0 = p->k;
     a.k1 = k_end;

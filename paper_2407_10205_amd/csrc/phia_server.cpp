@@ -6,9 +6,10 @@
 // state then stays resident until it retires.  The service thread runs
 // scheduling rounds: each round advances every running request by one chunk
 // of steps -- the split sweeps (16-bit and the largest int8 instances) in
-// launches of their own and the other column-split instances packed into one
-// cooperative launch, each with the device to itself (their workgroups wait
-// for each other), then what is left of the instances with N <= 512 in one
+// launches of their own while they are few, and the other column-split
+// instances, with these when they are many, packed into one cooperative
+// launch, each with the device to itself (their workgroups wait for each
+// other), then what is left of the instances with N <= 512 in one
 // batched launch on the service stream, overlapped with the resident (int8
 // that one CU holds) and VALU sweeps (ELL, FP32), whose own launches go round-robin to
 // three more streams -- then reads every request's best energy with one
@@ -26,8 +27,10 @@
 #include <condition_variable>
 #include <cstring>
 #include <deque>
+#include <map>
 #include <mutex>
 #include <new>
+#include <set>
 #include <thread>
 #include <tuple>
 #include <unordered_map>
@@ -123,6 +126,42 @@ void finish(phia_server* s, Request* r, int32_t state)
     s->in_use -= r->footprint;
 }
 
+// Estimates of a round's launches, in us per step.
+
+// A split sweep that runs alone: one pass takes 1.1 us and the products of its
+// k blocks, four replicas to a group with as many columns per member as their
+// number leaves (int8 N = 900, 1500 and 2000 1.3, 1.9 and 2.2 us; BF16 hi/lo
+// N = 600, 1000 and 2000 1.4, 1.6 and 3.3), sixteen with all waves at work
+// (256 replicas 2.0, 3.2 and 4.0; 2.3, 2.5 and 3.6).
+double split_us(const phia_problem* p)
+{
+    const Geometry& g = p->geo;
+    const double kb = p->Np / 64.0, columns = (p->Np / 16 + g.G - 1) / g.G;
+    const double pass = g.rows == 4 ? 1.1 + 0.0165 * g.planes * kb * columns / 4 : 1.3 + 0.07 * kb;
+    return pass * ((g.nblocks + g.ngroups - 1) / g.ngroups);
+}
+
+// A step of the column-split table launch of several requests: its latency,
+// which they share, the longest of int8 N = 900 and 2000 6.5 and 9.5 us with
+// one row tile to a block, 10.5 and 15 with two, BF16 hi/lo N = 600 and 2000 7
+// and 19, 12.5 and 19.5, and the couplings that each of their replica blocks
+// streams, together at 8 TB/s.
+int table_tiles(const phia_problem* p) { return p->R > 16 ? 2 : 1; }
+
+double table_us(const std::vector<Request*>& v)
+{
+    double latency = 0, bytes = 0;
+    for (const Request* r : v) {
+        const phia_problem* p = r->p;
+        const int mt = table_tiles(p);
+        const bool wide = p->path == PHIA_PATH_BF16HILO;
+        latency = std::max(latency, mt == 1 ? (wide ? 2.0 + p->N / 120.0 : 4.0 + p->N / 350.0)
+                                            : (wide ? 9.5 + p->N / 200.0 : 6.5 + p->N / 230.0));
+        bytes += static_cast<double>((p->R + 16 * mt - 1) / (16 * mt)) * p->Np * p->Np * (wide ? 4 : 1);
+    }
+    return latency + bytes / 8e6;
+}
+
 // One scheduling round over the running requests (service thread only).
 void round_once(phia_server* s, std::vector<Request*>& run)
 {
@@ -139,6 +178,38 @@ void round_once(phia_server* s, std::vector<Request*>& run)
     for (const Request* r : run)
         if (r->p->Np <= kBatchMaxNp && (r->p->geo.kind == 5 || r->p->geo.kind == 6)) ++own[r->p->geo.kind - 5];
     const bool batched[2] = {own[0] > 9, own[1] > 8};
+    // Large requests on the split sweep, one launch after the other, pay a whole
+    // step chain each, in the table they share one.  They go there where the
+    // estimates say so, per kernel of the table; requests that run there anyway
+    // count on both sides.  ms from submission to the last of n requests of 300
+    // steps, alone / in the table: int8 N = 900, 64 replicas 0.6 / 3.5 (n = 1),
+    // 4.0 / 5.3 (8), 8.0 / 7.0 (16), 15.9 / 9.0 (32); BF16 hi/lo N = 1000, 16
+    // replicas 0.6 / 3.7, 4.5 / 6.0, 9.0 / 7.4, 17.8 / 10.5; N = 2000, 64
+    // replicas 1.1 / 6.0, 8.5 / 11.3, 17.3 / 20, 35 / 38.
+    std::map<std::pair<int, int>, std::pair<std::vector<Request*>, std::vector<Request*>>> large;
+    std::set<const phia_problem*> tabled;
+    for (Request* r : run) {
+        const phia_problem* p = r->p;
+        if (p->Np <= kBatchMaxNp || p->k >= p->T) continue;
+        if (p->geo.kind == 6)
+            large[{p->path, table_tiles(p)}].first.push_back(r);
+        else if (p->geo.kind == 0 && p->geo.G > 1)
+            large[{p->path, table_tiles(p)}].second.push_back(r);
+    }
+    for (const auto& kv : large) {
+        const std::vector<Request*>& either = kv.second.first;
+        std::vector<Request*> all = kv.second.second;
+        double alone = table_us(all);
+        for (const Request* r : either) alone += split_us(r->p);
+        all.insert(all.end(), either.begin(), either.end());
+        if (table_us(all) >= alone) continue;
+        for (Request* r : either) {
+            if (prepare_table(r->p) != PHIA_OK)
+                r->failed = true;
+            else if (r->p->table.ok)
+                tabled.insert(r->p);
+        }
+    }
     for (Request* r : run) {
         phia_problem* p = r->p;
         const int64_t k_end = std::min(p->k + s->chunk, p->T);
@@ -147,7 +218,7 @@ void round_once(phia_server* s, std::vector<Request*>& run)
             (p->geo.kind == 0 || (p->geo.kind >= 5 && batched[p->geo.kind - 5]))) {
             small.push_back(p);
             small_end.push_back(k_end);
-        } else if (mfma && p->geo.kind == 0 && p->geo.G > 1) {
+        } else if ((mfma && p->geo.kind == 0 && p->geo.G > 1) || tabled.count(p)) {
             split.push_back(p);
             split_end.push_back(k_end);
         } else if (k_end > p->k) {
@@ -159,8 +230,13 @@ void round_once(phia_server* s, std::vector<Request*>& run)
     }
     // Other column-split instances: several per cooperative launch, with nothing
     // else on the device (the launches below wait for it).
-    if (!split.empty() && launch_group_chunk(split.data(), static_cast<int>(split.size()), split_end.data(), s->st,
-                                             s->gtab, s->gtab_cap) != PHIA_OK)
+    for (phia_problem* p : split)
+        if (tabled.count(p)) std::swap(p->geo, p->table);
+    const bool split_ok = split.empty() || launch_group_chunk(split.data(), static_cast<int>(split.size()),
+                                                              split_end.data(), s->st, s->gtab, s->gtab_cap) == PHIA_OK;
+    for (phia_problem* p : split)
+        if (tabled.count(p)) std::swap(p->geo, p->table);
+    if (!split_ok)
         for (Request* r : run)
             if (std::find(split.begin(), split.end(), r->p) != split.end()) r->failed = true;
     // The VALU and resident sweeps' launches on the auxiliary streams, after it.
