@@ -24,6 +24,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -128,6 +129,35 @@ void finish(phia_server* s, Request* r, int32_t state)
 
 // Estimates of a round's launches, in us per step.
 
+// A resident sweep beside others on the three auxiliary streams (N = 64 and
+// 512 0.5 and 1.2 us with FP4 operands, 0.53 and 1.42 with int8 ones), or by
+// itself where its workgroups take the whole device: one to a CU, four up to
+// 64 columns.
+double resident_us(const phia_problem* p)
+{
+    const double workgroups = p->geo.nblocks, device = p->N <= 64 ? 1024 : 256;
+    return (0.4 + p->N / (p->geo.fp4 ? 640.0 : 500.0)) * std::max(1.0 / 3, workgroups / device);
+}
+
+// The batched launch of several requests: the longest of its items of 16
+// replicas (int8 N <= 128 1.6 us, 256 2.9, 512 5.4; BF16 hi/lo N <= 192 2.7,
+// 256 4.3, 512 10.7), by as many rounds as they take on the CUs, where small
+// items run two to a CU and overlap.
+double batched_us(const std::vector<Request*>& v)
+{
+    double item = 0, items = 0;
+    bool small = true;
+    for (const Request* r : v) {
+        const phia_problem* p = r->p;
+        item = std::max(item, p->path == PHIA_PATH_BF16HILO ? 2.7 + std::max(0, p->Np - 192) / 40.0
+                                                            : 1.6 + std::max(0, p->Np - 128) / 100.0);
+        items += (p->R + 15) / 16;
+        small = small && p->Np <= 256;
+    }
+    const double rounds = items / 256;
+    return item * std::max(1.0, small ? rounds : std::ceil(rounds));
+}
+
 // A split sweep that runs alone: one pass takes 1.1 us and the products of its
 // k blocks, four replicas to a group with as many columns per member as their
 // number leaves (int8 N = 900, 1500 and 2000 1.3, 1.9 and 2.2 us; BF16 hi/lo
@@ -171,13 +201,32 @@ void round_once(phia_server* s, std::vector<Request*>& run)
     std::vector<std::pair<Request*, int64_t>> solo;  // VALU and resident sweeps (normal launches of their own)
     hipError_t e = hipSuccess;
     // Batch-sized instances take the launches of their own kind (resident or
-    // split sweep) while they are few: 0.4-1.2 us per step each, on three
-    // streams, or 1.3-1.5 one after the other, against 2.9-3.6 (int8) and 11
-    // us (BF16 hi/lo) for the batched launch of any number of them.
-    int own[2] = {0, 0};
-    for (const Request* r : run)
-        if (r->p->Np <= kBatchMaxNp && (r->p->geo.kind == 5 || r->p->geo.kind == 6)) ++own[r->p->geo.kind - 5];
-    const bool batched[2] = {own[0] > 9, own[1] > 8};
+    // split sweep) where the estimates say that these end before the batched
+    // launch would, per path and side of 256 columns (a launch each); requests
+    // that run there anyway count on both sides.  ms from submission to the
+    // last of n requests of 500 steps, own / batched, 64 replicas: int8 N = 256
+    // 2.2 / 2.4 (n = 9), 2.8 / 2.5 (12), 8.7 / 3.9 (40); BF16 hi/lo N = 130
+    // 3.1 / 1.8 (4), N = 512 3.3 / 7.3 (4), 7.4 / 7.7 (9), 16.2 / 8.8 (20); 1024
+    // replicas: int8 N = 256 4.7 / 4.1 (9), FP4 codes N = 512 6.8 / 10.2 (9).
+    std::map<std::pair<int, bool>, std::pair<std::vector<Request*>, std::vector<Request*>>> sized;
+    std::set<const phia_problem*> batched;
+    for (Request* r : run) {
+        const phia_problem* p = r->p;
+        if (p->Np > kBatchMaxNp || p->k >= p->T) continue;
+        if (p->geo.kind == 5 || p->geo.kind == 6)
+            sized[{p->path, p->Np > 256}].first.push_back(r);
+        else if (p->geo.kind == 0)
+            sized[{p->path, p->Np > 256}].second.push_back(r);
+    }
+    for (const auto& kv : sized) {
+        const std::vector<Request*>& either = kv.second.first;
+        std::vector<Request*> all = kv.second.second;
+        double own = batched_us(all);
+        for (const Request* r : either) own += r->p->geo.kind == 5 ? resident_us(r->p) : split_us(r->p);
+        all.insert(all.end(), either.begin(), either.end());
+        if (batched_us(all) < own)
+            for (const Request* r : either) batched.insert(r->p);
+    }
     // Large requests on the split sweep, one launch after the other, pay a whole
     // step chain each, in the table they share one.  They go there where the
     // estimates say so, per kernel of the table; requests that run there anyway
@@ -214,8 +263,7 @@ void round_once(phia_server* s, std::vector<Request*>& run)
         phia_problem* p = r->p;
         const int64_t k_end = std::min(p->k + s->chunk, p->T);
         const bool mfma = p->path == PHIA_PATH_I8 || p->path == PHIA_PATH_BF16HILO;
-        if (p->Np <= kBatchMaxNp && mfma &&
-            (p->geo.kind == 0 || (p->geo.kind >= 5 && batched[p->geo.kind - 5]))) {
+        if (p->Np <= kBatchMaxNp && mfma && (p->geo.kind == 0 || batched.count(p))) {
             small.push_back(p);
             small_end.push_back(k_end);
         } else if ((mfma && p->geo.kind == 0 && p->geo.G > 1) || tabled.count(p)) {

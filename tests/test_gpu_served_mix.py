@@ -75,3 +75,36 @@ def test_large_requests_share_launches():
         p.close()
     print("one", min(t[1]), "thirty-two", min(t[32]), flush=True)
     assert min(t[32]) < 0.7 * 32 * min(t[1])
+
+
+def test_batch_sized_requests_move_between_own_and_batched_launches():
+    """Batch-sized requests whose number crosses the line both ways, with and
+    without the accept/reject step (its state passes from sweep to sweep),
+    chunk ends within and at the ends of trajectories."""
+    check([("i8", 60 + 28 * i, (8, 21, 64)[i % 3], 50 + 40 * (i % 9), ((1.1, 0.9), None, (1.0, 1.0))[i % 3]) for i in range(16)] +
+          [("i8wide", 200 + 20 * i, 12, 300 - 20 * i, ((1.05, 0.95), None)[i % 2]) for i in range(6)], 22)
+    check([("bf16hilo", 130 + 40 * i, (5, 40)[i % 2], 45 + 60 * (i % 4), None) for i in range(9)], 9)
+    # admitted as others retire
+    check([("i8", 100 + 13 * i, 16, 75 + 30 * (i % 4), (1.1, 0.9) if i % 2 else None) for i in range(24)], 12)
+
+
+@pytest.mark.parametrize("n,N,R,most", [(4, 130, 16, 3.2), (12, 130, 64, 7.0), (4, 256, 1024, 3.2)])
+def test_few_small_16_bit_requests_share_launches(n, N, R, most):
+    """16-bit requests of few columns are batched from a few on: n of them end
+    before the launches of their own, one after the other, would."""
+    from paper_2407_10205_amd import phia as P
+    probs = [P.Problem(*make("bf16hilo", N, i % 3)) for i in range(n)]
+    t = {}
+    for m in (1, n):
+        srv = P.Server(1 << 36, max_slots=64, chunk_steps=100)
+        t[m] = []
+        for _ in range(4):
+            t0 = time.perf_counter()
+            for k in [srv.submit(p, R, 1500, -(1 << 60), seed=1, **SCHED) for p in probs[:m]]:
+                assert srv.wait(k, 60.0)["steps_used"] == 1500
+            t[m].append(time.perf_counter() - t0)
+        srv.close()
+    for p in probs:
+        p.close()
+    print(n, N, R, "one", min(t[1]), "all", min(t[n]), "ratio", min(t[n]) / min(t[1]), flush=True)
+    assert min(t[n]) < most * min(t[1])
