@@ -416,11 +416,13 @@ static bool make_geometry_pp(phia_problem* p, int R, int G, int fp4, Geometry& g
 static bool make_geometry_res(phia_problem* p, int R, Geometry& g)
 {
     if (p->path != PHIA_PATH_I8 || p->ikick) return false;
-    // Served requests past the batch sizes: from 64 replicas (N = 551 and 726,
-    // 64 replicas, 100 steps, in the column-split table 0.88 ms, on two
-    // auxiliary streams 0.17 ms; smaller ones stay in the table, by which the
-    // tests reach the read-out of its error words).
-    if (p->one_block_kernel && p->Np > kBatchMaxNp && R < 64) return false;
+    // Served requests past the batch sizes with up to 32 replicas stay in the
+    // column-split table, whose step they share and which more of them hardly
+    // lengthen.  ms for n requests of 500 steps, resident / table: N = 551, 16
+    // replicas 0.9 / 2.7 (n = 1), 3.5 / 4.4 (12), 8.6 / 6.0 (30), 32 replicas
+    // 0.9 / 4.1, 3.6 / 6.2, 8.6 / 7.7; N = 700, 16 replicas 9.8 / 7.2 (30), 48
+    // replicas 1.0 / 5.0, 4.1 / 7.1, 9.6 / 10.0, 256 replicas 9.9 / 22 (30).
+    if (p->one_block_kernel && p->Np > kBatchMaxNp && R <= 32) return false;
     const int64_t row = 2 * p->maxrow * p->N;  // bounds |sum_i s_i (I_i + h_i)|
     const int fp4 = p->has_j4 && row < (int64_t(1) << 24) && sweep_res_lds_bytes(p->N, 1) > 0;
     if (!fp4 && (row >= (int64_t(1) << 31) || sweep_res_lds_bytes(p->N, 0) == 0)) return false;

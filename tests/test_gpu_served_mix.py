@@ -77,6 +77,21 @@ def test_large_requests_share_launches():
     assert min(t[32]) < 0.7 * 32 * min(t[1])
 
 
+@pytest.mark.parametrize("N,R,want", [(520, 32, 0), (520, 33, 5), (700, 63, 5), (864, 33, 5)])
+def test_served_requests_that_one_cu_holds(N, R, want):
+    """Served requests past the batch sizes run resident from 33 replicas."""
+    from paper_2407_10205_amd import phia as P
+    J, h = make("i8", N, 1)
+    with P.Server(1 << 36, max_slots=4, chunk_steps=30) as srv, P.Problem(J, h) as p, P.Problem(J, h) as q:
+        t = srv.submit(p, R, 70, -(1 << 60), seed=5, **SCHED)
+        r = srv.wait(t, 60.0)
+        s = srv.spins(t)
+        assert p.info()["sweep_kernel"] == want
+        q.anneal(R, 70, seed=5, **SCHED)
+        e, _, k = q.best_exact()
+        assert (r["energy_units"], r["replica"]) == (e, k) and np.array_equal(s, q.replica_best()[1][k])
+
+
 def test_batch_sized_requests_move_between_own_and_batched_launches():
     """Batch-sized requests whose number crosses the line both ways, with and
     without the accept/reject step (its state passes from sweep to sweep),
