@@ -136,7 +136,7 @@ typedef struct {
                                workgroup (FP32 and ELL paths, I8 with the initial
                                kick); 5: the resident sweep, four replicas and all
                                columns per workgroup, the couplings held in one
-                               CU's registers and LDS (I8, N <= 512, or N <= 832
+                               CU's registers and LDS (I8, N <= 512, or N <= 864
                                with FP4 operands); 6: the split sweep, columns of
                                4 or 16 replicas over a group of workgroups with
                                the couplings in registers as int8 planes (FP32,
