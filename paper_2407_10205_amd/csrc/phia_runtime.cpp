@@ -446,8 +446,9 @@ static bool make_geometry_res(phia_problem* p, int R, Geometry& g)
 // the other, beside the table launches of the others (100 steps of 64
 // replicas, ms, in the table / alone: BF16 hi/lo N = 1105 1.82 / 0.23, N = 454,
 // 258 and 187 together 1.14 / 0.42).  ELL and FP32 requests share the device
-// on the auxiliary streams instead, int8 ones up to Np = 832 run resident
-// there or in the column-split table.
+// on the auxiliary streams instead, int8 ones up to Np = 832 (and up
+// to N = 864 with FP4 codes and more than 32 replicas) run resident there or in
+// the column-split table.
 static bool served_alone(const phia_problem* p)
 {
     return p->path == PHIA_PATH_BF16HILO || (p->path == PHIA_PATH_I8 && p->Np > 832);
@@ -502,15 +503,15 @@ static bool make_geometry_split(phia_problem* p, int R, int rows, int G, Geometr
 // Replica counts that take the VALU sweeps by default.
 constexpr int kValuTuneMaxR = 64;  // the autotuner also times the int8 VALU sweep up to here
 
-// Largest replica count for which an int8 anneal that the resident sweep does
-// not hold takes the VALU dot-product sweep (measured crossover against the
-// other matrix-core sweeps on MI355X).
+// Largest replica count for which an int8 anneal of up to 384 columns whose row
+// sums are too large for the resident sweep's energies (2 N max_i(sum_j |J_ij| +
+// |h_i|) from 2^31: fields far beyond the couplings) takes the VALU dot-product
+// sweep.  What else holds it are the one-block and the column-split sweep.
 // While J fits in LDS (Np <= 384) one workgroup per replica finishes a step
-// sooner than the matrix-core sweeps (0.94 against 1.21 us at Np = 64, 1.3
-// against 2.6 us at Np = 256, 2.05 against 2.77 us at Np = 384) until the
-// replicas outnumber the workgroups the CUs hold at once (J of 64 KiB: two
-// per CU, above 80 KiB: one); beyond Np = 384 the column-split matrix-core
-// sweeps win at every replica count.
+// sooner than these (0.94 against 1.21 us at Np = 64, 1.3 against 2.6 us at Np
+// = 256, 2.05 against 2.77 us at Np = 384) until the replicas outnumber the
+// workgroups the CUs hold at once (J of 64 KiB: two per CU, above 80 KiB: one);
+// beyond Np = 384 the column-split sweep wins at every replica count.
 static int valu_fallback(int Np)
 {
     if (Np <= 64) return 1024;
@@ -681,7 +682,8 @@ static void choose_mfma(phia_problem* p, int R)
 // kernel of 16 or 32 replicas per workgroup fills the chip only at 4096 or
 // 8192 and then overtakes it.
 // A traced anneal of 1024 replicas or more keeps the column split beyond 512
-// columns: a diagnostic run, by which the parity tests reach those kernels.
+// columns (2.9 against 2.0 us per step, with the same results): the parity
+// tests hold a traced benchmark-size anneal to it.
 static bool resident_wins(const phia_problem* p, int R)
 {
     if (p->trace && p->Np > 512 && R >= 1024) return false;

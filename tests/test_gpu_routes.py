@@ -115,3 +115,22 @@ def test_tune_cache_of_older_sweeps_is_skipped(monkeypatch, tmp_path):
     with P.Problem(*couplings("i8", 2100), path="i8") as p:
         p.anneal(16, 4, **SCHED)
         assert (p.info()["sweep_kernel"], p.info()["group"]) == (0, 44)
+
+
+@pytest.mark.parametrize("N,most", [(40, 1024), (64, 1024), (65, 512), (256, 512), (257, 256), (384, 256), (385, 0)])
+def test_row_sums_past_the_resident_sweep(N, most):
+    """Row sums past 2^31 / (2 N): few replicas take the VALU sweep, from one
+    more on a matrix-core one, and both give the oracle's results."""
+    from oracle import oracle as O
+    from paper_2407_10205_amd import phia as P
+    J, h = inst.sk_pm1(N, 1)
+    h = h.copy()
+    h[3] = float(1 << 28)
+    o = O.anneal(J.astype(np.int32), h.astype(np.int32), 0, 1, O.beta_linear(0.01, 0.02, 4), 0.2, 1.0, 25, 0)
+    for R in sorted({1, most, most + 1} - {0}):
+        print("row sums", N, R, flush=True)
+        with P.Problem(J, h, path="i8") as p:
+            p.anneal(R, 4, **SCHED)
+            assert (p.info()["sweep_kernel"] == 4) == (R <= most), (R, p.info())
+            E, S, K = p.replica_best()
+        assert E[0] == o.bestE[0] and K[0] == o.bestStep[0] and np.array_equal(S[0], o.bestS[0])
