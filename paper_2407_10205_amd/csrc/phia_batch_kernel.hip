@@ -9,8 +9,8 @@
 // cores, exact energy, records, kick), exactly as the other sweep kernels
 // compute it.
 //
-// Layout.  Eight waves; the products run transposed, D = J . S^T, with the
-// couplings as the A operand and the spins as the B operand of
+// Operands.  The products run transposed, D = J . S^T, with the couplings as
+// the A operand and the spins as the B operand of
 // v_mfma_scale_f32_16x16x128_f8f6f4 (FP4 x FP4, scales 1, FP32 accumulation
 // starting from the fields h): every product and partial sum is an integer
 // below 2^24 (host-checked), so the field is exact and stays in FP32 for the
@@ -20,15 +20,18 @@
 // replica's record, its energy partial (a sum over four lanes) and its spins
 // (four FP4 codes, one 16-bit LDS store) are then per-lane work; with a
 // column per lane and four replicas per lane they took 27 of the 55 VALU
-// instructions per spin-update.  Of ncb column blocks every wave owns ncb / 8
-// for both halves, and when four are left over wave w owns block w % 4 of
-// them for half w / 4, so that all waves carry the same number of tiles.
+// instructions per spin-update.  The couplings of the instance sit in LDS as
+// FP4 fragments for the whole item (128 KiB at Np = 512).
 //
-// The couplings of the instance sit in LDS as FP4 fragments for the whole
-// item (128 KiB at Np = 512), the spins of the step in two LDS buffers by
-// step parity, so a step has one barrier; the records of step k are taken in
-// step k + 1.  x is drawn here when an item starts a fresh anneal (no
-// separate init kernel).
+// Two forms.  A whole workgroup of sixteen waves runs one item as two teams of
+// eight, one per replica half, a phase apart: one spin buffer per half, two
+// barriers per step, the records taken in the step itself (team_item).  A squad
+// of eight waves runs an item of up to 256 columns with both halves: two spin
+// buffers by step parity, one barrier per step, the records of step k in step
+// k + 1; every wave owns ncb / 8 column blocks for both halves, and when four
+// are left over wave w owns block w % 4 of them for half w / 4, so that all
+// waves carry the same number of tiles; two squads share a workgroup
+// (squad_item).  x is drawn here when an item starts (no separate init kernel).
 //
 // The step is bound by VALU issue.  Its FP32 operations read VGPRs and inline
 // constants only (2 cycles per wave; 4 with an SGPR operand, see in_vgpr).
