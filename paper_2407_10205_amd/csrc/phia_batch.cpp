@@ -23,6 +23,19 @@
 
 using namespace phia;
 
+namespace phia {
+
+LaunchKey batch_key(const phia_problem* p)
+{
+    const int cbw = p->Np / 16 <= kWaves * 2 ? 2 : 4;
+    const int jl = sweep_batch_lds_bytes(p->path, p->Np, 1, p->mh) <= static_cast<size_t>(kLdsMax) ? 1 : 0;
+    return {p->path, cbw, jl, p->mh};
+}
+
+LaunchKey table_key(const phia_problem* p, const Geometry& g) { return {p->path, g.mt, g.cbw, p->mh}; }
+
+}  // namespace phia
+
 namespace {
 
 struct Bucket {
@@ -32,11 +45,11 @@ struct Bucket {
 };
 
 // Work items of steps [p->k, k_end) of problem p, added to its bucket.
-void add_items(phia_problem* p, int64_t k_end, std::map<std::tuple<int, int, int, int>, Bucket>& buckets)
+void add_items(phia_problem* p, int64_t k_end, std::map<LaunchKey, Bucket>& buckets)
 {
     const int ncb = p->Np / 16;
-    const int cbw = ncb <= kWaves * 2 ? 2 : 4;
-    const int jl = sweep_batch_lds_bytes(p->path, p->Np, 1, p->mh) <= static_cast<size_t>(kLdsMax) ? 1 : 0;
+    const LaunchKey key = batch_key(p);
+    const int cbw = std::get<1>(key), jl = std::get<2>(key);
     const int nblocks = (p->R + 15) / 16;
     SweepArgs a = sweep_args(p);
     a.inc = 0;  // table launches carry no flip-incremental variant
@@ -48,7 +61,7 @@ void add_items(phia_problem* p, int64_t k_end, std::map<std::tuple<int, int, int
     a.ncb = ncb;
     a.rows = 16;
     a.j_lds = jl;
-    Bucket& b = buckets[std::make_tuple(p->path, cbw, jl, p->mh)];
+    Bucket& b = buckets[key];
     b.path = p->path;
     b.cbw = cbw;
     b.jl = jl;
@@ -106,7 +119,7 @@ namespace phia {
 phia_status launch_batch_chunk(phia_problem* const* probs, int count, const int64_t* k_end, hipStream_t st,
                                SweepArgs*& dtab, size_t& cap)
 {
-    std::map<std::tuple<int, int, int, int>, Bucket> buckets;
+    std::map<LaunchKey, Bucket> buckets;
     for (int i = 0; i < count; ++i)
         if (k_end[i] > probs[i]->k) add_items(probs[i], k_end[i], buckets);
     std::vector<SweepArgs> tab;
@@ -159,12 +172,12 @@ phia_status launch_group_chunk(phia_problem* const* probs, int count, const int6
         std::vector<int> members;  // problem indices
         int nwg;
     };
-    std::map<std::tuple<int, int, int, int>, std::vector<int>> by_kernel;
+    std::map<LaunchKey, std::vector<int>> by_kernel;
     for (int i = 0; i < count; ++i) {
         const phia_problem* p = probs[i];
         if (k_end[i] <= p->k) continue;
         if (p->geo.kind != 0 || p->geo.G < 2) return fail(PHIA_EINVAL, "problem %d is not a column-split sweep", i);
-        by_kernel[std::make_tuple(p->path, p->geo.mt, p->geo.cbw, p->mh)].push_back(i);
+        by_kernel[table_key(p, p->geo)].push_back(i);
     }
     std::vector<Launch> launches;
     std::vector<int> alone;

@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <tuple>
+
 #include "phia.h"
 #include "phia_internal.h"
 
@@ -36,6 +38,7 @@ void clear_error();
 
 }  // namespace phia
 
+#include <tuple>
 #include <vector>
 
 namespace phia {
@@ -54,6 +57,11 @@ int valu_crossover(int Np);
 phia_status setup_mh_geometry(::phia_problem* p);
 SweepArgs sweep_args(const ::phia_problem* p);
 Geometry plain_geometry(::phia_problem* p, int R, int ikick = 0, bool split = true);
+// The launch that a problem's steps share with others' in a batched chunk, and
+// with others of the column-split table (geometry g).
+using LaunchKey = std::tuple<int, int, int, int>;
+LaunchKey batch_key(const ::phia_problem* p);
+LaunchKey table_key(const ::phia_problem* p, const Geometry& g);
 phia_status launch_batch_chunk(::phia_problem* const* probs, int count, const int64_t* k_end, hipStream_t st,
                                SweepArgs*& dtab, size_t& cap);
 phia_status launch_group_chunk(::phia_problem* const* probs, int count, const int64_t* k_end, hipStream_t st,

@@ -171,26 +171,41 @@ double split_us(const phia_problem* p)
     return pass * ((g.nblocks + g.ngroups - 1) / g.ngroups);
 }
 
-// A step of the column-split table launch of several requests: its latency,
-// which they share, the longest of int8 N = 900 and 2000 6.5 and 9.5 us with
-// one row tile to a block, 10.5 and 15 with two, BF16 hi/lo N = 600 and 2000 7
-// and 19, 12.5 and 19.5, and the couplings that each of their replica blocks
-// streams, together at 8 TB/s.
-int table_tiles(const phia_problem* p) { return p->R > 16 ? 2 : 1; }
+// A step of the column-split table launch, which its requests share, with mt
+// row tiles to a block: int8 N = 900 and 2000 6.5 and 9.5 us with one, 10.5 and
+// 15 with two; BF16 hi/lo N = 600 and 2000 7 and 19, 12.5 and 19.5.
+double latency_us(const phia_problem* p, int mt)
+{
+    if (p->path == PHIA_PATH_BF16HILO) return mt == 1 ? 2.0 + p->N / 120.0 : 9.5 + p->N / 200.0;
+    return mt == 1 ? 4.0 + p->N / 350.0 : 6.5 + p->N / 230.0;
+}
 
+// The couplings that each of a request's replica blocks streams, at 8 TB/s.
+double stream_us(const phia_problem* p, int blocks)
+{
+    return static_cast<double>(blocks) * p->Np * p->Np * (p->path == PHIA_PATH_BF16HILO ? 4 : 1) / 8e6;
+}
+
+// A step of several requests: the longest latency, as often as their
+// workgroups fill the CUs, and all that they stream.
 double table_us(const std::vector<Request*>& v)
 {
-    double latency = 0, bytes = 0;
+    double latency = 0, stream = 0, workgroups = 0;
     for (const Request* r : v) {
         const phia_problem* p = r->p;
-        const int mt = table_tiles(p);
-        const bool wide = p->path == PHIA_PATH_BF16HILO;
-        latency = std::max(latency, mt == 1 ? (wide ? 2.0 + p->N / 120.0 : 4.0 + p->N / 350.0)
-                                            : (wide ? 9.5 + p->N / 200.0 : 6.5 + p->N / 230.0));
-        bytes += static_cast<double>((p->R + 16 * mt - 1) / (16 * mt)) * p->Np * p->Np * (wide ? 4 : 1);
+        const Geometry& g = p->geo.kind == 6 ? p->table : p->geo;
+        latency = std::max(latency, latency_us(p, g.mt));
+        stream += stream_us(p, g.nblocks);
+        workgroups += g.ngroups * g.G;
     }
-    return latency + bytes / 8e6;
+    return latency * std::ceil(workgroups / 256) + stream;
 }
+
+// Requests that could run in one shared launch: those that may also run in
+// launches of their own, and those that only run there.
+struct Choice {
+    std::vector<Request*> either, shared;
+};
 
 // One scheduling round over the running requests (service thread only).
 void round_once(phia_server* s, std::vector<Request*>& run)
@@ -202,25 +217,25 @@ void round_once(phia_server* s, std::vector<Request*>& run)
     hipError_t e = hipSuccess;
     // Batch-sized instances take the launches of their own kind (resident or
     // split sweep) where the estimates say that these end before the batched
-    // launch would, per path and side of 256 columns (a launch each); requests
-    // that run there anyway count on both sides.  ms from submission to the
-    // last of n requests of 500 steps, own / batched, 64 replicas: int8 N = 256
-    // 2.2 / 2.4 (n = 9), 2.8 / 2.5 (12), 8.7 / 3.9 (40); BF16 hi/lo N = 130
-    // 3.1 / 1.8 (4), N = 512 3.3 / 7.3 (4), 7.4 / 7.7 (9), 16.2 / 8.8 (20); 1024
-    // replicas: int8 N = 256 4.7 / 4.1 (9), FP4 codes N = 512 6.8 / 10.2 (9).
-    std::map<std::pair<int, bool>, std::pair<std::vector<Request*>, std::vector<Request*>>> sized;
+    // launch would, per kernel of it (a launch each); requests that run there
+    // anyway count on both sides.  ms from submission to the last of n requests
+    // of 500 steps, own / batched, 64 replicas: int8 N = 256 2.2 / 2.4 (n = 9),
+    // 2.8 / 2.5 (12), 8.7 / 3.9 (40); BF16 hi/lo N = 130 3.1 / 1.8 (4), N = 512
+    // 3.3 / 7.3 (4), 7.4 / 7.7 (9), 16.2 / 8.8 (20); 1024 replicas: int8 N = 256
+    // 4.7 / 4.1 (9), FP4 codes N = 512 6.8 / 10.2 (9).
+    std::map<LaunchKey, Choice> sized;
     std::set<const phia_problem*> batched;
     for (Request* r : run) {
         const phia_problem* p = r->p;
         if (p->Np > kBatchMaxNp || p->k >= p->T) continue;
         if (p->geo.kind == 5 || p->geo.kind == 6)
-            sized[{p->path, p->Np > 256}].first.push_back(r);
+            sized[batch_key(p)].either.push_back(r);
         else if (p->geo.kind == 0)
-            sized[{p->path, p->Np > 256}].second.push_back(r);
+            sized[batch_key(p)].shared.push_back(r);
     }
     for (const auto& kv : sized) {
-        const std::vector<Request*>& either = kv.second.first;
-        std::vector<Request*> all = kv.second.second;
+        const std::vector<Request*>& either = kv.second.either;
+        std::vector<Request*> all = kv.second.shared;
         double own = batched_us(all);
         for (const Request* r : either) own += r->p->geo.kind == 5 ? resident_us(r->p) : split_us(r->p);
         all.insert(all.end(), either.begin(), either.end());
@@ -235,29 +250,46 @@ void round_once(phia_server* s, std::vector<Request*>& run)
     // 4.0 / 5.3 (8), 8.0 / 7.0 (16), 15.9 / 9.0 (32); BF16 hi/lo N = 1000, 16
     // replicas 0.6 / 3.7, 4.5 / 6.0, 9.0 / 7.4, 17.8 / 10.5; N = 2000, 64
     // replicas 1.1 / 6.0, 8.5 / 11.3, 17.3 / 20, 35 / 38.
-    std::map<std::pair<int, int>, std::pair<std::vector<Request*>, std::vector<Request*>>> large;
+    std::map<LaunchKey, Choice> large;
     std::set<const phia_problem*> tabled;
-    for (Request* r : run) {
+    // by row tiles and path: all of them alone, and the least that a table takes
+    // (without the latency where it runs anyway), so that geometries are looked
+    // for only where they may win
+    double own_us[2][5] = {}, least_us[2][5] = {}, stream[2][5] = {};
+    bool runs[2][5] = {};
+    for (const Request* r : run) {
         const phia_problem* p = r->p;
         if (p->Np <= kBatchMaxNp || p->k >= p->T) continue;
-        if (p->geo.kind == 6)
-            large[{p->path, table_tiles(p)}].first.push_back(r);
-        else if (p->geo.kind == 0 && p->geo.G > 1)
-            large[{p->path, table_tiles(p)}].second.push_back(r);
+        if (p->geo.kind == 0 && p->geo.G > 1) runs[p->geo.mt == 1 ? 0 : 1][p->path] = true;
+        if (p->geo.kind != 6) continue;
+        const int mt = p->R > 16 ? 2 : 1;
+        own_us[mt - 1][p->path] += split_us(p);
+        least_us[mt - 1][p->path] = std::max(least_us[mt - 1][p->path], latency_us(p, mt));
+        stream[mt - 1][p->path] += stream_us(p, (p->R + 16 * mt - 1) / (16 * mt));
+    }
+    for (Request* r : run) {
+        phia_problem* p = r->p;
+        if (p->Np <= kBatchMaxNp || p->k >= p->T) continue;
+        if (p->geo.kind == 6) {
+            const int row = p->R > 16 ? 1 : 0;
+            if (!p->table_tried && own_us[row][p->path] <= stream[row][p->path] + (runs[row][p->path] ? 0 : least_us[row][p->path]))
+                continue;
+            if (prepare_table(p) != PHIA_OK)
+                r->failed = true;
+            else if (p->table.ok)
+                large[table_key(p, p->table)].either.push_back(r);
+        } else if (p->geo.kind == 0 && p->geo.G > 1) {
+            large[table_key(p, p->geo)].shared.push_back(r);
+        }
     }
     for (const auto& kv : large) {
-        const std::vector<Request*>& either = kv.second.first;
-        std::vector<Request*> all = kv.second.second;
-        double alone = table_us(all);
-        for (const Request* r : either) alone += split_us(r->p);
+        const std::vector<Request*>& either = kv.second.either;
+        std::vector<Request*> all = kv.second.shared;
+        double own = table_us(all);
+        for (const Request* r : either) own += split_us(r->p);
         all.insert(all.end(), either.begin(), either.end());
-        if (table_us(all) >= alone) continue;
-        for (Request* r : either) {
-            if (prepare_table(r->p) != PHIA_OK)
-                r->failed = true;
-            else if (r->p->table.ok)
-                tabled.insert(r->p);
-        }
+        if (table_us(all) < own)
+            for (const Request* r : either) tabled.insert(r->p);
     }
     for (Request* r : run) {
         phia_problem* p = r->p;
