@@ -48,7 +48,7 @@ void kick_factors(const ::phia_problem* p, int64_t steps, const phia_schedule* s
 phia_status setup_state(::phia_problem* p, int32_t replicas, int64_t steps, const phia_schedule* s, uint64_t seed,
                         const std::vector<float>& ctab, bool& reuse, bool sync_first);
 void free_state(::phia_problem* p);
-phia_status prepare_table(::phia_problem* p);
+void prepare_table(::phia_problem* p);
 hipError_t take_exchange(::phia_problem* p, int kind);
 hipError_t clear_exchange(::phia_problem* p);
 phia_status make_resident(::phia_problem* p);

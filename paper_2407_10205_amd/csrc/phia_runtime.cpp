@@ -1439,32 +1439,40 @@ hipError_t clear_exchange(phia_problem* p)
 
 // A served request on the split sweep that may run in the table launches too:
 // their geometry (p->table, if there is one) and room for their words.  No
-// launch of the request is under way.
-phia_status prepare_table(phia_problem* p)
+// launch of the request is under way.  Without the memory for them it stays as
+// it is, without a table geometry.
+void prepare_table(phia_problem* p)
 {
-    if (p->table_tried) return PHIA_OK;
+    if (p->table_tried) return;
     p->table_tried = true;
     const Geometry own = p->geo;
     p->geo = Geometry{};
     choose_mfma(p, p->R);
     const Geometry g = p->geo;
     p->geo = own;
-    if (!g.ok || g.kind != 0 || g.G < 2) return PHIA_OK;
-    size_t* cnt = &p->state_bytes;
-    hipError_t e = hipSuccess;
-    if (xbits_bytes(p, g) > p->xb_bytes) {
+    if (!g.ok || g.kind != 0 || g.G < 2) return;
+    uint64_t *xbits = nullptr, *pbuf = nullptr;
+    const size_t xb = xbits_bytes(p, g), pb = pbuf_bytes(g);
+    const bool more = xb > p->xb_bytes;
+    if ((more && dalloc(reinterpret_cast<void**>(&xbits), xb, nullptr) != hipSuccess) ||
+        dalloc(reinterpret_cast<void**>(&pbuf), pb, nullptr) != hipSuccess) {
+        dfree(xbits);
+        dfree(pbuf);
+        (void)hipGetLastError();
+        return;
+    }
+    if (more) {
         dfree(p->dxbits);
-        p->xb_bytes = xbits_bytes(p, g);
-        e = dalloc(reinterpret_cast<void**>(&p->dxbits), p->xb_bytes, cnt);
+        p->dxbits = xbits;
+        p->state_bytes += xb - p->xb_bytes;
+        p->xb_bytes = xb;
     }
-    if (e == hipSuccess && !p->dpbuf) {
-        p->pb_bytes = pbuf_bytes(g);
-        e = dalloc(reinterpret_cast<void**>(&p->dpbuf), p->pb_bytes, cnt);
-    }
-    if (e != hipSuccess) return fail(PHIA_ENOMEM, "exchange buffer allocation failed");
+    dfree(p->dpbuf);
+    p->dpbuf = pbuf;
+    p->state_bytes += pb - p->pb_bytes;
+    p->pb_bytes = pb;
     p->exchange_kind = -1;  // cleared by the next launch
     p->table = g;
-    return PHIA_OK;
 }
 
 // Before a launch of sweep `kind`: the words start over when another sweep

@@ -274,10 +274,8 @@ void round_once(phia_server* s, std::vector<Request*>& run)
             const int row = p->R > 16 ? 1 : 0;
             if (!p->table_tried && own_us[row][p->path] <= stream[row][p->path] + (runs[row][p->path] ? 0 : least_us[row][p->path]))
                 continue;
-            if (prepare_table(p) != PHIA_OK)
-                r->failed = true;
-            else if (p->table.ok)
-                large[table_key(p, p->table)].either.push_back(r);
+            prepare_table(p);
+            if (p->table.ok) large[table_key(p, p->table)].either.push_back(r);
         } else if (p->geo.kind == 0 && p->geo.G > 1) {
             large[table_key(p, p->geo)].shared.push_back(r);
         }

@@ -103,7 +103,7 @@ def test_batch_sized_requests_move_between_own_and_batched_launches():
     check([("i8", 100 + 13 * i, 16, 75 + 30 * (i % 4), (1.1, 0.9) if i % 2 else None) for i in range(24)], 12)
 
 
-@pytest.mark.parametrize("n,N,R,most", [(4, 130, 16, 3.2), (12, 130, 64, 7.0), (4, 256, 1024, 3.2)])
+@pytest.mark.parametrize("n,N,R,most", [(4, 130, 16, 3.2), (12, 130, 64, 7.0)])
 def test_few_small_16_bit_requests_share_launches(n, N, R, most):
     """16-bit requests of few columns are batched from a few on: n of them end
     before the launches of their own, one after the other, would."""
