@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
     if constexpr (DERIV == 0 && kHeld) sk = sech2_in_vgprs();
     // accept/reject: the first lane of a replica's row in wave 0 decides
     ResMh* const sM = reinterpret_cast<ResMh*>(lds + kResMh);
-    const bool judge = MH && wave == 0 && lr == 0 && rok;
+    const bool decider = MH && wave == 0 && lr == 0 && rok;
     float lam = 1.0f;  // kHeld: the replica's multiplier
     if (MH && rok) lam = a.lam[rep];
     if (MH && tid < 4) sM->lam[tid] = 1.0f;
@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
     const bool writer = !FP4 || (lr & 4) == 0;
     const unsigned char* const arow = sS + static_cast<uint32_t>(lr >> 2) * srow + 16 * lg;
     __syncthreads();
-    if (judge) {
+    if (decider) {
         sM->q[4 + lg] = a.k0 > 0 ? static_cast<unsigned long long>(a.mhQ[rep]) : 0ull;
         sM->Es[lg] = a.mhE[rep * 2];
         sM->El[lg] = a.mhE[rep * 2 + 1];
@@ -259,7 +259,7 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
                     // to the trajectory's start where it was rejected.
                     kinetic(0);
                     __syncthreads();  // the kinetic units, the energy sums of step k - 1
-                    if (judge) {
+                    if (decider) {
                         const int64_t Ee = k > a.k0 ? energy(r3p * 4 + lg) : sM->El[lg];
                         const Decision d = res_decide(a.seed, static_cast<uint64_t>(a.r_base + rep), k / L - 1, sM->Es[lg],
                                                       Ee, static_cast<int64_t>(sM->q[lg] - sM->q[4 + lg]),
@@ -410,7 +410,7 @@ __global__ void __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_pe
         a.v[rep * Np + col] = v[i];
         a.bestS[rep * Np + col] = ((best >> i) & 1u) ? 1 : -1;
     }
-    if (judge) {
+    if (decider) {
         const int slot = static_cast<int>((a.k1 - 1) % 3) * 4 + lg;
         a.mhE[rep * 2] = sM->Es[lg];
         a.mhE[rep * 2 + 1] = FP4 ? static_cast<int64_t>(-0.5f * sEf[slot]) : -(sEi[slot] >> 1);
